@@ -294,8 +294,13 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) k_
         matern_add<PMAX, NT, FULL>(A.M, w, e, ch, L, t, par);
       };
     } else {
+      // (the reverse sweep keeps values of its own in the staging row: FENCE)
       auto inc1 = [&, n](int, int q) { return incv(n, q); };
-      return modes_noise<PMAX, FULL>(A.P, ch, inc1);
+      auto add = modes_noise<PMAX, NT, FULL, true>(A.P, ch, X.row0(), t, inc1);
+      return [&, n, add](int, double (&e)[PMAX]) {
+        if (n >= CS || (!dW && !dL)) return;
+        add(0, e);
+      };
     }
   };
   double* ck = A.ckpt + static_cast<size_t>(p) * nseg * 2 * nx;

@@ -71,21 +71,137 @@ struct AuxLds {
   static constexpr bool kInLds = 2 * kBytes <= 131072;  // both arrays
   static constexpr bool kDInLds = kBytes <= 65536;     // the explicit part
   double a[kInLds ? 2 : 1][kDInLds ? PMAX : 1][kDInLds ? NT : 1];
+  // the explicit part's PMAX NT words, free from a step's last solve to the
+  // next step's exchange (its readers have passed that solve's barriers)
+  __device__ double* row0() {
+    static_assert(kDInLds, "the explicit part is in LDS on every tile");
+    return &a[0][0][0];
+  }
 };
+
+// Node i of a row staged in LDS as a linear array lies at word
+// i ^ ((i >> 5) & 15) (doubles): a thread's chunk starts 2, 4, 8 or 16 words
+// after its neighbour's, which unswizzled would put 32 lanes on one or two
+// banks; the exclusive-or spreads them over all 32 double-width banks, and
+// keeps rows of consecutive nodes conflict-free.
+__device__ __forceinline__ int stage_pos(int i) { return i ^ ((i >> 5) & 15); }
+
+// Slots of the chunk from a row staged at stg (stage_pos).
+template <int PMAX, bool FULL>
+__device__ __forceinline__ double staged_slot(const double* stg, const Chunk& ch, int t, int j) {
+  if constexpr (FULL) {
+    // start = PMAX t: the exclusive-or touches the low bits only, where the
+    // slot index sits
+    const int b = 8 * stage_pos(PMAX * t);
+    return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(stg) + (b ^ (8 * j)));
+  } else {
+    return stg[stage_pos(ch.start + (slot_live<PMAX, FULL>(j, ch.cnt) ? j : 0))];
+  }
+}
 
 // The noise of the modes form: noise(n, e) adds sum_q xi_q inc(n, q) to the
 // chunk e, inc(n, q) being the increment dW^n_q (+ dLambda^n_q) of step n,
-// mode q.
-template <int PMAX, bool FULL, class IncF>
-__device__ __forceinline__ auto modes_noise(const StepParams& P, const Chunk& ch, IncF inc) {
-  return [&P, ch, inc](int n, double (&e)[PMAX]) {
-    for (int q = 0; q < P.n_modes; ++q) {
-      const double w = inc(n, q);
-      const double* xq = P.xi + static_cast<size_t>(q) * P.nx + ch.start;
+// mode q.  The mode table is read 16 bytes a lane with consecutive lanes on
+// consecutive nodes (thread t sums nodes 2 t, 2 t + 1, 2 t + 2 NT, ...) and
+// the sum changes hands through LDS.  A compute unit's address unit takes
+// about 20 clocks for a wavefront's load of 8 or of 16 bytes a lane while the
+// lanes share lines, and 64 where each lane has a line of its own, as in
+// reading the chunk's own nodes: 256 KB of table (Q = 8, nx = 4096) take a
+// workgroup 33900 clocks by chunks, 19600 by 8 and 10800 by 16 bytes a lane
+// (two workgroups a unit).  Chunks of at most four nodes are read as they are:
+// at least four of them share a line, and one wavefront alone waits longer for
+// the exchange than for the lines.  stg: PMAX NT doubles of LDS that no thread still
+// reads (FENCE: that the threads may still read, a barrier comes first).
+template <int PMAX, int NT, bool FULL, bool FENCE = false, class IncF>
+__device__ __forceinline__ auto modes_noise(const StepParams& P, const Chunk& ch, double* stg,
+                                            int t, IncF inc) {
+  static_assert(PMAX % 2 == 0, "nodes go in pairs");
+  return [&P, ch, stg, t0 = t, inc](int n, double (&e)[PMAX]) {
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    constexpr int H = PMAX / 2;  // pairs per thread
+    if constexpr (PMAX <= 4) {
+      for (int q = 0; q < P.n_modes; ++q) {
+        const double w = inc(n, q);
+        const double* xq = P.xi + static_cast<size_t>(q) * P.nx + ch.start;
 #pragma unroll
-      for (int j = 0; j < PMAX; ++j)
-        if (slot_live<PMAX, FULL>(j, ch.cnt)) e[j] = fma(xq[j], w, e[j]);
+        for (int j = 0; j < PMAX; ++j)
+          if (slot_live<PMAX, FULL>(j, ch.cnt)) e[j] = fma(xq[j], w, e[j]);
+      }
+      return;
     }
+    // laundered per step: the addresses below are the same for every step and
+    // would be hoisted out of the callers' step loops into spill slots
+    int t = t0;
+    Chunk own = ch;
+    asm volatile("" : "+v"(t), "+v"(own.start));
+    // uniform, also where the parameters come from memory (the batched runner):
+    // a descriptor in vector registers would be looped over lane by lane
+    const int nx = __builtin_amdgcn_readfirstlane(P.nx), Q = P.n_modes;
+    const uint64_t xi0 = reinterpret_cast<uint64_t>(P.xi);
+    const uint64_t xi = static_cast<uint64_t>(static_cast<uint32_t>(
+                            __builtin_amdgcn_readfirstlane(static_cast<int>(xi0 >> 32))))
+                            << 32 |
+                        static_cast<uint32_t>(
+                            __builtin_amdgcn_readfirstlane(static_cast<int>(xi0)));
+    // byte offset of pair k.  A ragged grid's pairs past the end read its last
+    // two nodes (unused, or for the single last node of an odd grid, taken
+    // from the pair's second half).  On full grids pairs share an address
+    // register as far as the instruction's 12-bit offset reaches.
+    constexpr int G = FULL && NT < 256 ? 256 / NT : 1;
+    constexpr int NV = (H + G - 1) / G;
+    int vo[NV];
+#pragma unroll
+    for (int g = 0; g < NV; ++g) {
+      const int i = 2 * (t + NT * G * g);
+      vo[g] = 8 * (FULL ? i : min(i, nx - 2));
+      asm volatile("" : "+v"(vo[g]));
+    }
+    auto fetch = [&](d2 (&x)[H], int q) {
+      const __amdgpu_buffer_rsrc_t row = __builtin_amdgcn_make_buffer_rsrc(
+          reinterpret_cast<double*>(xi) + static_cast<size_t>(q) * nx, 0, nx * 8, 0x00027000);
+#pragma unroll
+      for (int k = 0; k < H; ++k)
+        x[k] = __builtin_bit_cast(d2, __builtin_amdgcn_raw_buffer_load_b128(
+                                          row, vo[k / G] + 16 * NT * (k % G), 0, 0));
+    };
+    d2 acc[H];
+#pragma unroll
+    for (int k = 0; k < H; ++k) acc[k] = d2{0.0, 0.0};
+    auto add = [&](const d2 (&x)[H], double w) {
+#pragma unroll
+      for (int k = 0; k < H; ++k) {
+        acc[k].x = fma(x[k].x, w, acc[k].x);
+        acc[k].y = fma(x[k].y, w, acc[k].y);
+      }
+    };
+    // two rows in turn, one in flight while the other is summed (past the last
+    // row the last one is read again and enters with weight 0: a branch around
+    // the loads would end the overlap)
+    d2 xa[H], xb[H];
+    fetch(xa, 0);
+    for (int q = 0; q < Q; q += 2) {
+      const int q1 = q + 1 < Q ? q + 1 : q;
+      const double wa = inc(n, q), w1 = inc(n, q1), wb = q + 1 < Q ? w1 : 0.0;
+      fetch(xb, q1);
+      add(xa, wa);
+      fetch(xa, q + 2 < Q ? q + 2 : q1);
+      add(xb, wb);
+    }
+    if (FENCE) __syncthreads();
+    // stage_pos(2 t + 2 NT k): 2 t and 2 NT k share no bits.  Words past nx take
+    // values that are not used, and the dead slots of a ragged chunk repeat
+    // its first node's.
+    const int p0 = stage_pos(2 * t);
+#pragma unroll
+    for (int k = 0; k < H; ++k) {
+      const int c = p0 ^ ((NT / 16 * k) & 15);
+      const bool single = !FULL && 2 * k + 2 > kMinRows<PMAX> && 2 * (t + NT * k) == nx - 1;
+      stg[2 * NT * k + c] = single ? acc[k].y : acc[k].x;
+      stg[2 * NT * k + (c ^ 1)] = acc[k].y;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < PMAX; ++j) e[j] += staged_slot<PMAX, FULL>(stg, own, t, j);
   };
 }
 
@@ -473,8 +589,8 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) k_
       if (dL) w += dL[n * Q + q];
       return w;
     };
-    st = run_window<PMAX, NT, FULL>(A.P, K, modes_noise<PMAX, FULL>(A.P, ch, inc), A.n_steps, m,
-                                    u, ch, L, X, t, par, iters);
+    st = run_window<PMAX, NT, FULL>(A.P, K, modes_noise<PMAX, NT, FULL>(A.P, ch, X.row0(), t, inc),
+                                    A.n_steps, m, u, ch, L, X, t, par, iters);
   }
   store_chunk<PMAX, FULL>(mp, ch, m);
   store_chunk<PMAX, FULL>(up, ch, u);
@@ -645,8 +761,9 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) k_
         if (lam) w += lam[n * Q + q];
         return w;
       };
-      st = run_window<PMAX, NT, FULL, false>(A.P, K, modes_noise<PMAX, FULL>(A.P, ch, inc), S, m,
-                                             u, ch, L, X, t, par, iters);
+      st = run_window<PMAX, NT, FULL, false>(A.P, K,
+                                             modes_noise<PMAX, NT, FULL>(A.P, ch, X.row0(), t, inc),
+                                             S, m, u, ch, L, X, t, par, iters);
     }
     double girs = 0.0;  // this thread's share of the Girsanov term (after the window: not
                         // live across the solver loop)
