@@ -297,14 +297,16 @@ int launch_jitter(const sch_model& md, const Tile& tl, const sch_obs& ob, uint64
     A.M = *M;
     A.stage = zeta;
   }
-  const size_t dyn = M ? 0 : 2 * sizeof(double) * static_cast<size_t>(n_steps) * md.n_modes;
-  if (dyn > 32768) return fail(SCH_E_SHAPE, "n_steps * n_modes too large for the jitter kernel");
+  const size_t dyn = M ? 0 : sizeof(double) * static_cast<size_t>(n_steps) * md.n_modes;
+  if (2 * dyn > 32768) return fail(SCH_E_SHAPE, "n_steps * n_modes too large for the jitter kernel");
   const HelmConst K = make_helm(md, tl);
   return with_tile(tl, [&]<int PM, int NT, bool FULL>() -> int {
-    // the workgroup's LDS (static solver and window arrays plus the
-    // increments) must fit the 160 KiB of a compute unit
-    constexpr size_t kStatic = sizeof(RowLds<NT>) + sizeof(AuxLds<PM, NT>);
-    if (kStatic + dyn > 160 * 1024)
+    // the workgroup's LDS (solver and window arrays plus the increments, here
+    // counted twice: current and proposed) must fit the 160 KiB of a compute
+    // unit; kStatic bounds the arrays' sizes from below, dyn's share covers the rest
+    constexpr size_t kStatic = 294 * sizeof(double) * (NT / kWave) + sizeof(AuxLds<PM, NT>);
+    static_assert(sizeof(RowLds<NT>) + sizeof(AuxLds<PM, NT>) <= 156 * 1024, "LDS");
+    if (kStatic + 2 * dyn > 160 * 1024)
       return fail(SCH_E_SHAPE, "n_steps * n_modes too large for the jitter kernel at nx = %d",
                   md.nx);
     if (M && dLam)

@@ -151,25 +151,23 @@ __device__ __forceinline__ double wave_max(double v) {
   v = vmax(v, dpp_f64b<kDppRowBcast31, 0xc>(v));
   return readlane_f64(v, 63);
 }
-// An upper bound, within a relative 2^-20, of the wave's maximum of
-// nonnegative doubles: the maximum of the high words, each raised by one
-// unit where the low word is not zero.  The 32-bit maximum fuses with the
-// lane moves (one instruction per row step instead of three).
-__device__ __forceinline__ double wave_max_bound(double v) {
+// In lane 63: the maximum over the wave of the high words of nonnegative
+// doubles, each raised by one unit where the low word is not zero: the high
+// word of an upper bound, within a relative 2^-20, of the wave's maximum.  The
+// 32-bit maximum fuses with the lane moves, one instruction a step.
+__device__ __forceinline__ uint32_t wave_max_word(double v) {
   uint32_t h = static_cast<uint32_t>(__double2hiint(v)) + (__double2loint(v) != 0 ? 1u : 0u);
-  h = max(h, static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(h), kDppRowShr + 1,
-                                                            0xf, 0xf, true)));
-  h = max(h, static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(h), kDppRowShr + 2,
-                                                            0xf, 0xf, true)));
-  h = max(h, static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(h), kDppRowShr + 4,
-                                                            0xf, 0xf, true)));
-  h = max(h, static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(h), kDppRowShr + 8,
-                                                            0xf, 0xf, true)));
-  const uint32_t m = max(max(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(h), 15)),
-                             static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(h), 31))),
-                         max(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(h), 47)),
-                             static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(h), 63))));
-  return __hiloint2double(static_cast<int>(m), 0);
+#define SCH_STEP(CTRL, ROWS)                                                                 \
+  h = max(h, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(h), CTRL, \
+                                                               ROWS, 0xf, false)));
+  SCH_STEP(kDppRowShr + 1, 0xf)
+  SCH_STEP(kDppRowShr + 2, 0xf)
+  SCH_STEP(kDppRowShr + 4, 0xf)
+  SCH_STEP(kDppRowShr + 8, 0xf)
+  SCH_STEP(kDppRowBcast15, 0xa)
+  SCH_STEP(kDppRowBcast31, 0xc)
+#undef SCH_STEP
+  return h;
 }
 __device__ __forceinline__ int wave_or(int v) {
   v |= dpp_i32<kDppRowShr + 1>(v, 0);
@@ -196,7 +194,16 @@ struct RowLds {
   double etail[3][W];          // last-row spike values of each wavefront's last chunk
   double edge[2][W][6];        // wavefront edge values of halo exchanges, double buffered
   double red[3][W];            // workgroup reductions
-  double helm[2][W][8];        // per-wavefront records of solve_helm()
+  // per-wavefront records of solve_helm(), double buffered: the scans' totals,
+  // the factor of the wavefront's rows (ragged grids), and the reduction that
+  // rides along
+  double hrec[2][W][2];
+  double hmul[2][W];
+  double hscale[2][W];
+  uint32_t hword[2][W];
+  // lane factors of solve_helm() on full grids: [0] the model's operator,
+  // [1] the Matern-type noise's
+  double tab[2][3][kWave];
 };
 
 template <int NT>

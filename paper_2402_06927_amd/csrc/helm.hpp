@@ -9,11 +9,10 @@
 // F+_i = f_i + r F+_{i-1} and F-_i = f_i + r F-_{i+1}.  Both recurrences are
 // linear scans: each thread scans its chunk, the chunk carries are combined
 // across lanes by DPP row shifts and readlane and across wavefronts through
-// one LDS record per wavefront, and the periodic images add r^(i+1) G+_{N-1} / (1 - r^N) (resp.
-// r^(N-i) G-_0 / (1 - r^N)) to the non-periodic scans G+-.  The record also
-// carries three nonnegative reduction partials, so a caller can fold a
-// workgroup max-reduction into the same barrier; the first comes back as
-// +infinity when the right-hand side holds a non-finite value.
+// one LDS record per wavefront; the carry into a wavefront is the sum over all
+// wavefronts' totals in cyclic order, its own the farthest, over 1 - r^N.  The
+// record also carries a reduction (HelmRed), so a caller can fold a workgroup
+// maximum into the same barrier.
 #pragma once
 
 #include "device.hpp"
@@ -27,16 +26,14 @@ struct HelmConst {
   double rb, rb1;   // r^base, r^(base+1): multipliers of chunks of base / base+1 rows
   int base;         // nx / NT
   double ho, hd;    // off-diagonal and diagonal of H
+  double iho;       // 1 / ho
   // The mass matrix M (rows h/6, 2h/3, h/6) lies in the span of I and H:
   // M = beta H + gamma I with beta = (h/6) / ho, gamma = 2h/3 - beta hd, so
   // H^{-1} M f = beta f + gamma H^{-1} f = mg (F+ + F-) + mf f with
   // mg = gamma coef and mf = beta - gamma coef (the scan form below).
   double mg, mf;
   double mh6, mh23;  // h/6 and 2h/3
-  // rb^e for e = 0..64, formed on the host by the same binary powering as
-  // the solve's own (the products rb^(2^i) in increasing i): the PWT solves
-  // read the lane scans' factors from this table
-  double pwt[65];
+  double pwt[65];  // rb^e for e = 0..64: the lane scans' factors on full grids
 };
 
 // Composition of affine carries: apply (m1, c1) then (m2, c2).
@@ -62,124 +59,98 @@ __device__ __forceinline__ void scan_rows(double& m, double& c) {
   }
 }
 
-// Scans of the per-wavefront records held in lanes 0..W-1 (W <= 8): forward
-// and backward affine compositions and running maxima of three nonnegative
-// partials (lanes without a partner contribute the identities 1, 0 and 0).
-template <int W>
-__device__ __forceinline__ void record_scan(double& f0, double& f1, double& b0, double& b1,
-                                            double& q0, double& q1, double& q2) {
-#define SCH_RSTEP(D)                                                              \
-  if constexpr (W > D) {                                                          \
-    double pm = dpp_f64<kDppRowShr + D>(f0, 1.0), pc = dpp_f64z<kDppRowShr + D>(f1); \
-    compose(pm, pc, f0, f1, f0, f1);                                              \
-    double qm = dpp_f64<kDppRowShl + D>(b0, 1.0), qc = dpp_f64z<kDppRowShl + D>(b1); \
-    compose(qm, qc, b0, b1, b0, b1);                                              \
-    q0 = vmax(q0, dpp_f64z<kDppRowShr + D>(q0));                                  \
-    q1 = vmax(q1, dpp_f64z<kDppRowShr + D>(q1));                                  \
-    q2 = vmax(q2, dpp_f64z<kDppRowShr + D>(q2));                                  \
+// Lane factors of the scans on full grids, where every chunk has PMAX rows and
+// the factor of any run of e chunks is rb^e: [0] joins the odd rows of 16
+// lanes to the row before, [1] the upper 32 lanes to the lower, [2] the lane's
+// distance from the wavefront's first.  The backward scans read the same
+// tables mirrored.  In LDS, because in registers they are 12 a thread for the
+// whole kernel, and the kernels have none to spare.
+__device__ __forceinline__ void helm_table(const HelmConst& K, double (&tab)[3][kWave], int t) {
+  if (t < kWave) {
+    tab[0][t] = (t & 16) ? K.pwt[(t & 15) + 1] : 0.0;
+    tab[1][t] = t >= 32 ? K.pwt[t - 31] : 0.0;
+    tab[2][t] = K.pwt[t];
   }
-  SCH_RSTEP(1)
-  SCH_RSTEP(2)
-  SCH_RSTEP(4)
-#undef SCH_RSTEP
 }
 
+// Reduction that rides on a solve's barrier: in, the thread's share of the
+// change (and of the scale, on the first iteration, when `first`) and whether
+// its elimination failed; out, the workgroup's word, the same in every
+// thread: kUnstable if an elimination failed anywhere, at least kNonfinite if
+// the right-hand side holds a value that is not finite, else the high word of
+// an upper bound within 2^-20 of the maximum change; and the maximum scale.
+struct HelmRed {
+  double diff, scale;
+  bool bad, first;
+  uint32_t word;
+};
+constexpr uint32_t kUnstable = 0xffffffffu, kNonfinite = 0x7ff00000u;
+
 // MASS: u = H^{-1} M f instead of H^{-1} f, with fl, fr the values of f at
-// the nodes bordering the chunk (for the bordering values of u).
-// PWT (full chunks): the lane scans' powers of r^PMAX are loaded from K.pwt
-// at every call instead of being formed per lane.  Formed powers are loop
-// invariants that the compiler hoists out of the caller's loops into
-// registers; where registers are short (the kernels with the Matern-type
-// noise, which also hold that operator's powers) they are spilled and
-// reloaded from scratch every iteration, and loading them from the table
-// is cheaper.  Elsewhere forming them costs fewer instructions.  Both give
-// the same bits.
-template <int PMAX, int NT, bool FULL, bool MASS = false, bool PWT = false, class LT>
-__device__ __forceinline__ void solve_helm(const HelmConst& K, const double (&f)[PMAX],
-                                           double (&u)[PMAX], double& uL, double& uR, int cnt,
-                                           LT& L, int slot, int t, double red0, double red1,
-                                           double red2, double& gred0, double& gred1,
-                                           double& gred2, double fl = 0.0, double fr = 0.0) {
+// the nodes bordering the chunk (for the bordering values of u).  tab: the
+// operator's lane factors (helm_table; read on full grids).
+//
+// Per chunk and direction one scan for the carry out of it, the lanes' scan of
+// those carries, the wavefronts' totals through LDS behind one barrier, and
+// the scan again from the carry into the chunk.  What bounds it is the number
+// of vector instructions (about 65 besides the rows' own on full grids, 150
+// when the records were scanned across lanes with their maxima and the rows of
+// 16 lanes joined by selects), so the periodic sum over the wavefronts is a
+// plain Horner sum that every lane forms for itself from the records, read
+// from LDS in the wavefront's own rotation.
+template <int PMAX, int NT, bool FULL, bool MASS = false, bool RED = false>
+__device__ __forceinline__ void solve_helm(const HelmConst& K, const double (&tab)[3][kWave],
+                                           const double (&f)[PMAX], double (&u)[PMAX], double& uL,
+                                           double& uR, int cnt, RowLds<NT>& L, int slot, int t,
+                                           HelmRed& R, double fl = 0.0, double fr = 0.0) {
   constexpr int W = NT / kWave;
   const int lane = t & (kWave - 1), wv = t / kWave;
   const double r = K.r;
   // carries out of the chunk: the local forward scan at its last node and
   // the local backward scan at its first node
-  double acc = 0.0;
+  double fc = 0.0, bc = 0.0;
 #pragma unroll
-  for (int j = 0; j < PMAX; ++j) acc = slot_live<PMAX, FULL>(j, cnt) ? fma(r, acc, f[j]) : acc;
-  const double cpl = acc;
-  acc = 0.0;
+  for (int j = 0; j < PMAX; ++j) fc = slot_live<PMAX, FULL>(j, cnt) ? fma(r, fc, f[j]) : fc;
 #pragma unroll
-  for (int j = PMAX - 1; j >= 0; --j) acc = slot_live<PMAX, FULL>(j, cnt) ? fma(r, acc, f[j]) : acc;
-  const double cmn = acc;
-  const double mth = (FULL || cnt == K.base) ? K.rb : K.rb1;
-  const int row = lane >> 4;
-  double fc = cpl, bc = cmn;          // offsets of the inclusive scans
-  double xfm, xfc, xbm, xbc;          // exclusive carries within the wavefront
-  double tfm, tfc, tbm, tbc;          // wavefront totals
+  for (int j = PMAX - 1; j >= 0; --j) bc = slot_live<PMAX, FULL>(j, cnt) ? fma(r, bc, f[j]) : bc;
+  uint32_t word = 0;
+  double scale = 0.0;
+  if constexpr (RED) {
+    word = wave_max_word(R.diff);
+    if (R.first) scale = wave_max(R.scale);
+  }
+  // inclusive scans over the wavefront, then the exclusive carries (xf*, xb*)
+  double xfm, xfc, xbm, xbc, tm;
   if constexpr (FULL) {
-    // Every chunk has PMAX rows, so the factor of any run of lanes is a
-    // power of r^PMAX: only the offsets need cross-lane steps.
-    const double* pt = K.pwt;
-    int ln = lane;
-    if constexpr (PWT) {
-      // opaque indices keep the loads at the call (scalar loads for the
-      // uniform powers, four vector loads of the table for the per-lane ones)
-      int z = 0;
-      asm volatile("" : "+s"(z));
-      pt += z;
-      asm volatile("" : "+v"(ln));
-    }
-    const double rb = PWT ? pt[1] : K.rb, rb2 = PWT ? pt[2] : rb * rb,
-                 rb4 = PWT ? pt[4] : rb2 * rb2, rb8 = PWT ? pt[8] : rb4 * rb4,
-                 rb16 = PWT ? pt[16] : rb8 * rb8, rb32 = rb16 * rb16,
-                 rb64 = PWT ? pt[64] : rb32 * rb32;
-    auto pw = [&](int e) {  // rb^e, 0 <= e <= 64
-      if constexpr (PWT) return pt[e];
-      double p = (e & 1) ? rb : 1.0;
-      p *= (e & 2) ? rb2 : 1.0;
-      p *= (e & 4) ? rb4 : 1.0;
-      p *= (e & 8) ? rb8 : 1.0;
-      p *= (e & 16) ? rb16 : 1.0;
-      p *= (e & 32) ? rb32 : 1.0;
-      return (e & 64) ? p * rb64 : p;
-    };
-    const int i16 = ln & 15;
+    const double rb = K.rb, rb2 = K.pwt[2], rb4 = K.pwt[4], rb8 = K.pwt[8];
+    const int ml = kWave - 1 - lane;
+    const double a1 = tab[0][lane], a2 = tab[1][lane], b1 = tab[0][ml], b2 = tab[1][ml];
+    xfm = tab[2][lane];
+    xbm = tab[2][ml];
+    tm = K.pwt[64];
     fc = fma(rb, dpp_f64z<kDppRowShr + 1>(fc), fc);
-    fc = fma(rb2, dpp_f64z<kDppRowShr + 2>(fc), fc);
-    fc = fma(rb4, dpp_f64z<kDppRowShr + 4>(fc), fc);
-    fc = fma(rb8, dpp_f64z<kDppRowShr + 8>(fc), fc);
     bc = fma(rb, dpp_f64z<kDppRowShl + 1>(bc), bc);
+    fc = fma(rb2, dpp_f64z<kDppRowShr + 2>(fc), fc);
     bc = fma(rb2, dpp_f64z<kDppRowShl + 2>(bc), bc);
+    fc = fma(rb4, dpp_f64z<kDppRowShr + 4>(fc), fc);
     bc = fma(rb4, dpp_f64z<kDppRowShl + 4>(bc), bc);
+    fc = fma(rb8, dpp_f64z<kDppRowShr + 8>(fc), fc);
     bc = fma(rb8, dpp_f64z<kDppRowShl + 8>(bc), bc);
-    {
-      const double r0c = readlane_f64(fc, 15), r1c = readlane_f64(fc, 31),
-                   r2c = readlane_f64(fc, 47);
-      const double p2c = fma(rb16, r0c, r1c), p3c = fma(rb16, p2c, r2c);
-      const double pc = row == 0 ? 0.0 : row == 1 ? r0c : row == 2 ? p2c : p3c;
-      fc = fma(pw(i16 + 1), pc, fc);
-      const double t1c = readlane_f64(bc, 16), t2c = readlane_f64(bc, 32),
-                   t3c = readlane_f64(bc, 48);
-      const double h1c = fma(rb16, t3c, t2c), h0c = fma(rb16, h1c, t1c);
-      const double hc = row == 3 ? 0.0 : row == 2 ? t3c : row == 1 ? h1c : h0c;
-      bc = fma(pw(16 - i16), hc, bc);
-    }
-    xfm = pw(ln);
-    xfc = dpp_f64z<kDppWaveShr1>(fc);
-    xbm = pw(kWave - 1 - ln);
-    xbc = dpp_f64z<kDppWaveShl1>(bc);
-    tfm = rb64;
-    tfc = readlane_f64(fc, kWave - 1);
-    tbm = rb64;
-    tbc = readlane_f64(bc, 0);
+    // rows of 16 in pairs, then halves (the factors of the lanes that take
+    // nothing are 0; there is no backward broadcast, so its sources go
+    // through scalar registers)
+    const double h0 = readlane_f64(bc, 16), h2 = readlane_f64(bc, 48);
+    fc = fma(a1, dpp_f64z<kDppRowBcast15>(fc), fc);
+    bc = fma(b1, lane < 32 ? h0 : h2, bc);
+    const double h1 = readlane_f64(bc, 32);
+    fc = fma(a2, dpp_f64z<kDppRowBcast31>(fc), fc);
+    bc = fma(b2, h1, bc);
   } else {
-    // Inclusive scans over the lanes, forward (lanes 0..lane) and backward
-    // (lanes lane..63): Hillis-Steele steps inside each 16-lane row by DPP
-    // row shifts (identity where the row has no partner), then the rows are
-    // joined with the row results read from the row ends into scalar
-    // registers.
+    // Hillis-Steele steps inside each 16-lane row by DPP row shifts (identity
+    // where the row has no partner), then the rows are joined with the row
+    // results read from the row ends into scalar registers.
+    const double mth = cnt == K.base ? K.rb : K.rb1;
+    const int row = lane >> 4;
     double fm = mth, bm = mth;
     scan_rows<kDppRowShr>(fm, fc);
     scan_rows<kDppRowShl>(bm, bc);
@@ -203,75 +174,74 @@ __device__ __forceinline__ void solve_helm(const HelmConst& K, const double (&f)
       const double hc = row == 3 ? 0.0 : row == 2 ? t3c : row == 1 ? h1c : h0c;
       compose(hm, hc, bm, bc, bm, bc);
     }
-    // exclusive values within the wavefront (identity at the ends)
+    // exclusive factors within the wavefront (identity at the ends)
     xfm = dpp_f64<kDppWaveShr1>(fm, 1.0);
-    xfc = dpp_f64z<kDppWaveShr1>(fc);
     xbm = dpp_f64<kDppWaveShl1>(bm, 1.0);
-    xbc = dpp_f64z<kDppWaveShl1>(bc);
-    tfm = readlane_f64(fm, kWave - 1);
-    tfc = readlane_f64(fc, kWave - 1);
-    tbm = readlane_f64(bm, 0);
-    tbc = readlane_f64(bc, 0);
+    tm = fm;  // lane 63: the wavefront's
   }
-  // wavefront totals and reduction partials to LDS
-  if (lane == 0) {
-    double* rec = L.helm[slot][wv];
-    rec[0] = tfm;
-    rec[1] = tfc;
-    rec[2] = tbm;
-    rec[3] = tbc;
-    rec[4] = red0;
-    rec[5] = red1;
-    rec[6] = red2;
+  xfc = dpp_f64z<kDppWaveShr1>(fc);
+  xbc = dpp_f64z<kDppWaveShl1>(bc);
+  if constexpr (RED) {
+    // the wavefront's forward total (lane 63) is finite iff every f_j is
+    word = fabs(fc) <= 1.7976931348623157e308 ? word : kNonfinite;
+    if (__any(R.bad)) word = kUnstable;
   }
-  __syncthreads();
-  // Combine the W records: lane v < W of every wavefront takes record v
-  // (identities elsewhere); forward records compose left to right, backward
-  // ones right to left, by DPP steps inside row 0; the values this wavefront
-  // needs are read back with readlane.
-  double f0 = 1.0, f1 = 0.0, b0 = 1.0, b1 = 0.0, q0 = 0.0, q1 = 0.0, q2 = 0.0;
-  if (lane < W) {
-    const double* rec = L.helm[slot][lane];
-    f0 = rec[0];
-    f1 = rec[1];
-    b0 = rec[2];
-    b1 = rec[3];
-    q0 = rec[4];
-    q1 = rec[5];
-    q2 = rec[6];
+  // carries into the wavefront: the periodic sums over all wavefronts' totals,
+  // farthest (its own) first, over 1 - r^N
+  double cf, cb;
+  if constexpr (W == 1) {
+    cf = readlane_f64(fc, kWave - 1);
+    cb = readlane_f64(bc, 0);
+    if constexpr (RED) {
+      R.word = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(word), kWave - 1));
+      R.scale = scale;
+    }
+  } else {
+    if (lane == kWave - 1) {
+      L.hrec[slot][wv][0] = fc;
+      if constexpr (!FULL) L.hmul[slot][wv] = tm;
+      if constexpr (RED) {
+        L.hword[slot][wv] = word;
+        if (R.first) L.hscale[slot][wv] = scale;
+      }
+    }
+    if (lane == 0) L.hrec[slot][wv][1] = bc;
+    __syncthreads();
+    const int w0 = __builtin_amdgcn_readfirstlane(wv);
+    double rf[W], rbk[W], rm[W];
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+      const int v = (w0 + i) & (W - 1);
+      rf[i] = L.hrec[slot][v][0];
+      rbk[i] = L.hrec[slot][v][1];
+      rm[i] = FULL ? tm : L.hmul[slot][v];
+    }
+    if constexpr (RED) {
+      uint32_t m = L.hword[slot][0];
+#pragma unroll
+      for (int i = 1; i < W; ++i) m = max(m, L.hword[slot][i]);
+      R.word = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(m)));
+      if (R.first) {
+        R.scale = L.hscale[slot][0];
+#pragma unroll
+        for (int i = 1; i < W; ++i) R.scale = fmax(R.scale, L.hscale[slot][i]);
+      }
+    }
+    cf = rf[0];
+    cb = rbk[0];
+#pragma unroll
+    for (int i = 1; i < W; ++i) {
+      cf = fma(rm[i], cf, rf[i]);
+      cb = fma(rm[W - i], cb, rbk[W - i]);
+    }
   }
-  record_scan<W>(f0, f1, b0, b1, q0, q1, q2);
-  gred0 = readlane_f64(q0, W - 1);
-  gred1 = readlane_f64(q1, W - 1);
-  gred2 = readlane_f64(q2, W - 1);
-  const double allfc = readlane_f64(f1, W - 1);
-  // the row's forward total is finite iff every f_j is: a non-finite input
-  // reports gred0 = +infinity
-  if (!(fabs(allfc) <= 1.7976931348623157e308)) gred0 = INFINITY;
-  const double allbc = readlane_f64(b1, 0);
-  const int wvu = __builtin_amdgcn_readfirstlane(wv);
-  double inm = 1.0, inc = 0.0, rim = 1.0, ric = 0.0;
-  if (wvu > 0) {
-    inm = readlane_f64(f0, wvu - 1);
-    inc = readlane_f64(f1, wvu - 1);
-  }
-  if (wvu + 1 < W) {
-    rim = readlane_f64(b0, wvu + 1);
-    ric = readlane_f64(b1, wvu + 1);
-  }
-  // thread-exclusive carries: forward carry at node start-1, product r^start;
-  // backward carry at node end+1, product r^(nx - end - 1)
-  double pfm, pfc, pbm, pbc;
-  compose(inm, inc, xfm, xfc, pfm, pfc);
-  compose(rim, ric, xbm, xbc, pbm, pbc);
-  // periodic images: Gamma+ = G+_{N-1} / (1 - r^N), Gamma- = G-_0 / (1 - r^N)
-  const double gamp = allfc * K.rN1, gamm = allbc * K.rN1;
-  const double Ep = fma(pfm, gamp, pfc);
-  const double Em = fma(pbm, gamm, pbc);
+  // thread-exclusive carries, at the nodes bordering the chunk
+  const double Ep = fma(xfm, cf * K.rN1, xfc);
+  const double Em = fma(xbm, cb * K.rN1, xbc);
   // the global scans inside the chunk, rerun from the carries into it:
   // F+_j = f_j + r F+_{j-1} from F+_{start-1} = Ep, F-_j = f_j + r F-_{j+1}
   // from F-_{end+1} = Em; u_j = coef (F+_j + F-_j - f_j)
-  acc = Ep;
+  double acc = Ep;
 #pragma unroll
   for (int j = 0; j < PMAX; ++j) {
     acc = slot_live<PMAX, FULL>(j, cnt) ? fma(r, acc, f[j]) : acc;
@@ -300,9 +270,19 @@ __device__ __forceinline__ void solve_helm(const HelmConst& K, const double (&f)
   }
   const double g0 = MASS ? fma(K.mh6, fl + f[1], K.mh23 * f[0]) : f[0];
   const double gl = MASS ? fma(K.mh6, flm + fr, K.mh23 * fla) : fla;
-  const double iho = 1.0 / K.ho;
+  const double iho = K.iho;
   uL = (g0 - K.hd * u[0] - K.ho * u[1]) * iho;
   uR = (gl - K.hd * ul - K.ho * ulm) * iho;
+}
+
+// The same without a reduction.
+template <int PMAX, int NT, bool FULL, bool MASS = false>
+__device__ __forceinline__ void solve_helm(const HelmConst& K, const double (&tab)[3][kWave],
+                                           const double (&f)[PMAX], double (&u)[PMAX], double& uL,
+                                           double& uR, int cnt, RowLds<NT>& L, int slot, int t,
+                                           double fl = 0.0, double fr = 0.0) {
+  HelmRed none{};
+  solve_helm<PMAX, NT, FULL, MASS, false>(K, tab, f, u, uL, uR, cnt, L, slot, t, none, fl, fr);
 }
 
 }  // namespace sch

@@ -232,15 +232,14 @@ __device__ __forceinline__ void matern_add(const MaternDev& M, const double (&w)
   double r[PMAX], U[PMAX];
 #pragma unroll
   for (int j = 0; j < PMAX; ++j) r[j] = M.load * (left_of<PMAX, FULL>(w, j, wl) + w[j]);
-  double uL = 0.0, uR = 0.0, g0, g1, g2;
+  double uL = 0.0, uR = 0.0;
   for (int i = 0; i < M.k; ++i) {
     if (i > 0) {
       double hl = uL, hr = uR;
       if (!bordered) halo<PMAX, NT, FULL>(U, cnt, L, t, hl, hr, par.hs);
       mass_apply_h<PMAX, FULL>(U, r, M.h, cnt, hl, hr, 1.0);
     }
-    solve_helm<PMAX, NT, FULL, false, true>(M.K, r, U, uL, uR, cnt, L, par.slot, t, 0.0, 0.0, 0.0,
-                                            g0, g1, g2);
+    solve_helm<PMAX, NT, FULL>(M.K, L.tab[1], r, U, uL, uR, cnt, L, par.slot, t);
     par.slot ^= 1;
   }
 #pragma unroll
@@ -262,15 +261,14 @@ __device__ __forceinline__ void matern_transpose(const MaternDev& M, const doubl
   double r[PMAX], z[PMAX];
 #pragma unroll
   for (int j = 0; j < PMAX; ++j) r[j] = g[j];
-  double zL = 0.0, zR = 0.0, g0, g1, g2;
+  double zL = 0.0, zR = 0.0;
   for (int i = 0; i < M.k; ++i) {
     if (i > 0) {
       double hl = zL, hr = zR;
       if (!bordered) halo<PMAX, NT, FULL>(z, cnt, L, t, hl, hr, par.hs);
       mass_apply_h<PMAX, FULL>(z, r, M.h, cnt, hl, hr, 1.0);
     }
-    solve_helm<PMAX, NT, FULL, false, true>(M.K, r, z, zL, zR, cnt, L, par.slot, t, 0.0, 0.0, 0.0,
-                                            g0, g1, g2);
+    solve_helm<PMAX, NT, FULL>(M.K, L.tab[1], r, z, zL, zR, cnt, L, par.slot, t);
     par.slot ^= 1;
   }
   double hl = zL, hr = zR;
@@ -302,10 +300,8 @@ __device__ __forceinline__ void matern_transpose(const MaternDev& M, const doubl
 // the last iterate is kept, on a non-finite iterate or a system whose
 // elimination growth exceeds kMaxGrowth (SCH_E_UNSTABLE) the step's input is
 // kept (KEEP) or the state is left undefined (!KEEP, for callers that discard
-// a failed window: u^n then need not stay live through the iteration).  PWT
-// selects the table form of the Helmholtz solve (solve_helm), which the
-// kernels with the Matern-type noise take.
-template <int PMAX, int NT, bool FULL, bool KEEP = true, bool PWT = false, class NoiseF>
+// a failed window: u^n then need not stay live through the iteration).
+template <int PMAX, int NT, bool FULL, bool KEEP = true, class NoiseF>
 __device__ int run_window(const StepParams& P, const HelmConst& K, NoiseF noise, int n_steps,
                           double (&m)[PMAX], double (&u)[PMAX], const Chunk& ch, RowLds<NT>& L,
                           AuxLds<PMAX, NT>& X, int t, Parity& par, int& iters) {
@@ -415,7 +411,6 @@ __device__ int run_window(const StepParams& P, const HelmConst& K, NoiseF noise,
           }
           setP(j, ms[j]);
         }
-        scale = wave_max(scale);
       } else {
 #pragma unroll
         for (int j = 0; j < PMAX; ++j) {
@@ -424,24 +419,24 @@ __device__ int run_window(const StepParams& P, const HelmConst& K, NoiseF noise,
           setP(j, ms[j]);
         }
       }
-      // an upper bound within 2^-20 (a few units of the tolerance's last
-      // digit): the test below can only stop later, never earlier
-      diff = wave_max_bound(diff);
-      // u* = H^{-1} M m* (the mass product folded into the scan form)
-      // the growth test rides on the Helmholtz record as a wave-uniform flag
-      const double wbad = __any(!(grow <= kMaxGrowth)) ? 1.0 : 0.0;
-      double gdiff, gscale, gbad;
-      solve_helm<PMAX, NT, FULL, true, PWT>(K, ms, us, uL, uR, cnt, L, par.slot, t, diff, scale,
-                                            wbad, gdiff, gscale, gbad, sl - mL, sr - mR);
+      // u* = H^{-1} M m* (the mass product folded into the scan form).  The
+      // change comes back as an upper bound within 2^-20 (a few units of the
+      // tolerance's last digit): the test below can only stop later, never
+      // earlier.
+      HelmRed R{diff, scale, !(grow <= kMaxGrowth), k == 1, 0};
+      solve_helm<PMAX, NT, FULL, true, true>(K, L.tab[0], ms, us, uL, uR, cnt, L, par.slot, t, R,
+                                             sl - mL, sr - mR);
       par.slot ^= 1;
-      if (gbad > 0.0) {
+      if (R.word == kUnstable) {
         status = SCH_E_UNSTABLE;
         break;
       }
-      if (!(gdiff < INFINITY)) {
+      if (R.word >= kNonfinite) {
         status = SCH_E_NONFINITE;
         break;
       }
+      const double gdiff = __hiloint2double(static_cast<int>(R.word), 0);
+      const double gscale = R.scale;
       if (k == 1) lim = P.tol * gscale;
       // stop once the iterate's error is within tolerance: for a contraction
       // with ratio c, |m* - m_k| <= c / (1 - c) |m_k - m_{k-1}|; c is the ratio
@@ -565,6 +560,9 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) k_
   const Chunk ch = chunk_of<NT>(A.P.nx, t);
   double* mp = A.m + static_cast<size_t>(p) * A.P.nx;
   double* up = A.u + static_cast<size_t>(p) * A.P.nx;
+  helm_table(K, L.tab[0], t);
+  if constexpr (MATERN) helm_table(A.M.K, L.tab[1], t);
+  __syncthreads();
   double m[PMAX], u[PMAX];
   load_chunk<PMAX, FULL>(mp, ch, m);
   load_chunk<PMAX, FULL>(up, ch, u);
@@ -578,7 +576,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) k_
       load_chunk<PMAX, FULL>(cells + static_cast<size_t>(n) * nx, ch, w);
       matern_add<PMAX, NT, FULL>(A.M, w, e, ch, L, t, par);
     };
-    st = run_window<PMAX, NT, FULL, true, true>(A.P, K, noise, A.n_steps, m, u, ch, L, X, t, par,
+    st = run_window<PMAX, NT, FULL, true>(A.P, K, noise, A.n_steps, m, u, ch, L, X, t, par,
                                                 iters);
   } else {
     const int Q = A.P.n_modes;
@@ -701,7 +699,7 @@ template <int PMAX, int NT, bool FULL, bool MATERN = false, bool MCTRL = false>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) k_jitter(const JitterArgs A, const HelmConst K) {
   __shared__ RowLds<NT> L;
   __shared__ AuxLds<PMAX, NT> X;
-  extern __shared__ double dyn[];  // modes: [2][n_steps][n_modes]: current increments, proposal
+  extern __shared__ double dyn[];  // modes: the proposal [n_steps][n_modes]
   const int p = blockIdx.x, t = threadIdx.x;
   const int nx = A.P.nx, Q = A.P.n_modes, S = A.n_steps;
   const Chunk ch = chunk_of<NT>(nx, t);
@@ -713,16 +711,19 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) k_
     cur = dWp;
     prop = A.stage + static_cast<size_t>(p) * S * nx;
   } else {
-    cur = dyn;
-    prop = dyn + S * Q;
+    // the current increments stay in the caller's row (every thread reads back
+    // only what it wrote): two workgroups share a compute unit's LDS
     dWp = A.dW + static_cast<size_t>(p) * S * Q;
-    for (int i = t; i < S * Q; i += NT) cur[i] = dWp[i];
+    cur = dWp;
+    prop = dyn;
   }
   double phi = A.phi[p];
   const double theta = *A.theta;
   const double srho = sqrt(1.0 - A.rho * A.rho);
   int acc = 0, iters = 0;
   Parity par;
+  helm_table(K, L.tab[0], t);
+  if constexpr (MATERN) helm_table(A.M.K, L.tab[1], t);
   __syncthreads();
   for (int j = 0; j < A.n_jitter; ++j) {
     const uint32_t w3 = (A.temper_k << 16) | static_cast<uint32_t>(j);
@@ -754,7 +755,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) k_
           }
         matern_add<PMAX, NT, FULL>(A.M, w, e, ch, L, t, par);
       };
-      st = run_window<PMAX, NT, FULL, false, true>(A.P, K, noise, S, m, u, ch, L, X, t, par, iters);
+      st = run_window<PMAX, NT, FULL, false>(A.P, K, noise, S, m, u, ch, L, X, t, par, iters);
     } else {
       auto inc = [&](int n, int q) {
         double w = prop[n * Q + q];
@@ -839,9 +840,6 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) k_
       const size_t len = static_cast<size_t>(S) * nx;
       for (size_t i = t; i < len; i += NT) dWp[i] = cur[i];
     }
-  } else {
-    if (acc > 0)
-      for (int i = t; i < S * Q; i += NT) dWp[i] = cur[i];
   }
   if (t == 0) {
     A.phi[p] = phi;
@@ -872,6 +870,8 @@ __global__ void __launch_bounds__(NT) k_paper_init(const StepParams P, const Mat
     e[j] = 0.0;
   }
   Parity par;
+  helm_table(M.K, L.tab[1], t);
+  __syncthreads();
   matern_add<PMAX, NT, FULL>(M, w, e, ch, L, t, par);
   double a, b;
   normal2(seed, static_cast<uint32_t>(p), 1u, tag, 0u, a, b);
@@ -893,6 +893,8 @@ __global__ void __launch_bounds__(NT) k_matern_field(const StepParams P, const M
 #pragma unroll
   for (int j = 0; j < PMAX; ++j) e[j] = 0.0;
   Parity par;
+  helm_table(M.K, L.tab[1], t);
+  __syncthreads();
   matern_add<PMAX, NT, FULL>(M, w, e, ch, L, t, par);
   store_chunk<PMAX, FULL>(out + static_cast<size_t>(p) * P.nx, ch, e);
 }
@@ -916,9 +918,10 @@ __global__ void __launch_bounds__(NT) k_helmholtz(const HelmArgs A, const HelmCo
   if (A.mode == 0) {
     // the mass product folded into the scan form (the bordering values are
     // not used)
-    double uL, uR, g0, g1, g2;
-    solve_helm<PMAX, NT, FULL, true>(K, v, o, uL, uR, ch.cnt, L, 0, t, 0.0, 0.0, 0.0, g0, g1, g2,
-                                     0.0, 0.0);
+    double uL, uR;
+    helm_table(K, L.tab[0], t);
+    __syncthreads();
+    solve_helm<PMAX, NT, FULL, true>(K, L.tab[0], v, o, uL, uR, ch.cnt, L, 0, t);
   } else {
     // right-hand side H u = M u + alpha^2 K u, then the mass solve
     double hl, hr;
