@@ -148,14 +148,14 @@ __device__ int adjoint_step(const StepParams& P, const HelmConst& K, NoiseF nois
   auto s_at = [&](double (&sv)[PMAX]) {
 #pragma unroll
     for (int j = 0; j < PMAX; ++j) {
-      double x = X.a[1][kL ? j : 0][kL ? t : 0];
+      double x = X.at(kL ? 1 : 0, j, t);
       asm volatile("" : "+v"(x));
       sv[j] = x;
     }
   };
   auto lam_at = [&](int j) -> double {
     if constexpr (kL) {
-      double x = X.a[0][j][t];
+      double x = X.at(0, j, t);
       asm volatile("" : "+v"(x));
       return x;
     } else {
@@ -168,8 +168,8 @@ __device__ int adjoint_step(const StepParams& P, const HelmConst& K, NoiseF nois
     nu[j] = 0.0;
     rhs[j] = lam[j];
     if constexpr (kL) {
-      X.a[0][j][t] = lam[j];
-      X.a[1][j][t] = s[j];
+      X.at(0, j, t) = lam[j];
+      X.at(1, j, t) = s[j];
     }
   }
   // the first solve gives A^{-T} lambda; picard_max corrections follow at most

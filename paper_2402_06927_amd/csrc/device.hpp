@@ -105,6 +105,9 @@ __device__ __forceinline__ double dpp_f64b(double src) {
   const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(src), CTRL, ROWS, 0xf, false);
   return __hiloint2double(hi, lo);
 }
+// The value of the lane before / after, around the wavefront's ends.
+__device__ __forceinline__ double wave_prev(double v) { return dpp_f64z<0x13C>(v); }
+__device__ __forceinline__ double wave_next(double v) { return dpp_f64z<0x134>(v); }
 // lane must be wave-uniform
 __device__ __forceinline__ double readlane_f64(double v, int lane) {
   const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
@@ -379,14 +382,76 @@ __device__ __forceinline__ void spike_eliminate(const double (&A)[E], const doub
   }
 }
 
+// The interface equations A s_prev + B s + C s_next = R are close to diagonal
+// where chunks are long: a coupling falls by a factor per row (0.41 at the
+// 4096-node workloads, so 5e-7 over 16 rows).  Where every |A| + |C| is below
+// eps |B|, K sweeps s <- (R - A s_prev - C s_next) / B from s = R / B leave an
+// error below eps^(K+1) of the largest unknown; these bounds give 2^-57, a
+// sixteenth of the rounding of the result.
+struct SweepEnds {
+  double prev, next;
+};
+constexpr double kSweep2 = 0x1.0p-19, kSweep4 = 3.4e-4, kSweep6 = 3.4e-3;
+
+// The same system over the 64 lanes of one wavefront, lane l holding equation
+// l (periodic): sweeps where they suffice, cyclic reduction levels (which
+// square the couplings and double the distance d of the coupled lanes) until
+// they do.  The first level moves its values by lane rotations; the farther
+// ones by ds_bpermute.  Returns s of the lane.
+__device__ __forceinline__ double interface_wave(double A, double B, double C, double R,
+                                                 int lane) {
+  auto level = [&](auto prev, auto next) {
+    const double Am = prev(A), Bm = prev(B), Cm = prev(C), Rm = prev(R);
+    const double Ap = next(A), Bp = next(B), Cp = next(C), Rp = next(R);
+    const double q1 = A * rcp64(Bm), q2 = C * rcp64(Bp);
+    A = -q1 * Am;
+    B = B - q1 * Cm - q2 * Ap;
+    C = -q2 * Cp;
+    R = R - q1 * Rm - q2 * Rp;
+  };
+  double s = 0.0;
+  // true, with s set, if the couplings are small enough for sweeps
+  auto sweep = [&](auto prev, auto next) {
+    const double e = fabs(A) + fabs(C), b = fabs(B);
+    if (__any(!(e <= kSweep4 * b))) return false;
+    const bool four = __any(!(e <= kSweep2 * b));
+    const double inv = rcp64(B), a = A * inv, c = C * inv, z = R * inv;
+    s = z;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) s = fma(-a, prev(s), fma(-c, next(s), z));
+    if (four) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k) s = fma(-a, prev(s), fma(-c, next(s), z));
+    }
+    return true;
+  };
+  {
+    auto prev = [](double v) { return wave_prev(v); };
+    auto next = [](double v) { return wave_next(v); };
+    if (sweep(prev, next)) return s;
+    level(prev, next);
+  }
+#pragma unroll 1
+  for (int d = 2; d < kWave; d <<= 1) {
+    const int lm = (lane - d) & (kWave - 1), lp = (lane + d) & (kWave - 1);
+    auto prev = [&](double v) { return bperm_f64(v, lm); };
+    auto next = [&](double v) { return bperm_f64(v, lp); };
+    if (sweep(prev, next)) return s;
+    level(prev, next);
+  }
+  // after every level each equation couples s_l to itself only
+  return R * rcp64(A + B + C);
+}
+
 // Solve of the periodic tridiagonal interface system of the NT chunks,
 //   A_t s_{t-1} + B_t s_t + C_t s_{t+1} = R_t   (t mod NT),
 // redundantly by every wavefront: lane l holds the E = NT/64 consecutive
 // equations E l .. E l + E - 1 in eA..eR, eliminates all but the first by
 // the partition method, and the 64 remaining equations (one per lane,
-// periodic) are solved by cyclic reduction across the lanes (ds_bpermute),
-// stopping once every coupling is below 2^-60 of its diagonal.  Returns, for
-// the calling thread t = 64 w + lane, s_t, s_{t+1} and s_{t-1}.
+// periodic) are solved by interface_wave().  Returns, for the calling thread
+// t = 64 w + lane, s_t, s_{t+1} and s_{t-1}.  For NT > 64 where couplings are
+// too strong for sweeps across the chunks themselves (short chunks, large
+// dv).
 template <int NT>
 __device__ __forceinline__ void interface_solve(const double (&eA)[NT / kWave],
                                                 const double (&eB)[NT / kWave],
@@ -394,6 +459,7 @@ __device__ __forceinline__ void interface_solve(const double (&eA)[NT / kWave],
                                                 const double (&eR)[NT / kWave], int t, double& s,
                                                 double& snext, double& sprev, double& grow) {
   constexpr int E = NT / kWave;
+  static_assert(E > 1, "several wavefronts");
   const int lane = t & (kWave - 1);
   double y[E], g[E], k[E];
   y[0] = 0.0;
@@ -401,10 +467,8 @@ __device__ __forceinline__ void interface_solve(const double (&eA)[NT / kWave],
   k[0] = 0.0;
   spike_eliminate<E>(eA, eB, eC, eR, y, g, k, grow);
   // run tails: the last unknown in terms of (z_0, z_E); first interior row
-  const double yT = E > 1 ? y[E - 1] : 0.0, gT = E > 1 ? g[E - 1] : 1.0,
-               kT = E > 1 ? k[E - 1] : 0.0;
-  const double y1 = E > 1 ? y[1 < E ? 1 : 0] : 0.0, g1 = E > 1 ? g[1 < E ? 1 : 0] : 0.0,
-               k1 = E > 1 ? k[1 < E ? 1 : 0] : 1.0;
+  const double yT = y[E - 1], gT = g[E - 1], kT = k[E - 1];
+  const double y1 = y[1], g1 = g[1], k1 = k[1];
   // tails of lane l-1 (periodic over the 64 lanes)
   double pY = dpp_f64z<kDppWaveShr1>(yT), pG = dpp_f64z<kDppWaveShr1>(gT),
          pK = dpp_f64z<kDppWaveShr1>(kT);
@@ -415,38 +479,11 @@ __device__ __forceinline__ void interface_solve(const double (&eA)[NT / kWave],
     pG = lane == 0 ? wg : pG;
     pK = lane == 0 ? wk : pK;
   }
-  double A = eA[0] * pG;
-  double B = fma(eA[0], pK, fma(eC[0], g1, eB[0]));
-  double C = eC[0] * k1;
-  double R = fma(-eA[0], pY, fma(-eC[0], y1, eR[0]));
-  double z = 0.0;
-  {
-    bool done = false;
-#pragma unroll 1
-    for (int d = 1; d < kWave; d <<= 1) {
-      if (!__any(fabs(A) + fabs(C) > 0x1.0p-60 * fabs(B))) {
-        z = R * rcp64(B);
-        done = true;
-        break;
-      }
-      const int lm = (lane - d) & (kWave - 1), lp = (lane + d) & (kWave - 1);
-      const double Am = bperm_f64(A, lm), Bm = bperm_f64(B, lm), Cm = bperm_f64(C, lm),
-                   Rm = bperm_f64(R, lm);
-      const double Ap = bperm_f64(A, lp), Bp = bperm_f64(B, lp), Cp = bperm_f64(C, lp),
-                   Rp = bperm_f64(R, lp);
-      const double q1 = A * rcp64(Bm), q2 = C * rcp64(Bp);
-      const double nA = -q1 * Am;
-      const double nB = B - q1 * Cm - q2 * Ap;
-      const double nC = -q2 * Cp;
-      const double nR = R - q1 * Rm - q2 * Rp;
-      A = nA;
-      B = nB;
-      C = nC;
-      R = nR;
-    }
-    // after every level each equation couples z_l to itself only
-    if (!done) z = R * rcp64(A + B + C);
-  }
+  const double A = eA[0] * pG;
+  const double B = fma(eA[0], pK, fma(eC[0], g1, eB[0]));
+  const double C = eC[0] * k1;
+  const double R = fma(-eA[0], pY, fma(-eC[0], y1, eR[0]));
+  const double z = interface_wave(A, B, C, R, lane);
   // the run's unknowns
   const double zn = [&] {
     const double v = dpp_f64z<kDppWaveShl1>(z), w0 = readlane_f64(z, 0);
@@ -459,14 +496,11 @@ __device__ __forceinline__ void interface_solve(const double (&eA)[NT / kWave],
   // thread t = 64 w + lane owns unknown t, held by lane t / E, slot lane % E
   const int wu = __builtin_amdgcn_readfirstlane(t / kWave);
   const int src = (kWave / E) * wu + lane / E;
-  double sv = zr[0];
-  if constexpr (E > 1) {
-    sv = bperm_f64(zr[0], src);
+  double sv = bperm_f64(zr[0], src);
 #pragma unroll
-    for (int e = 1; e < E; ++e) {
-      const double v = bperm_f64(zr[e], src);
-      sv = (lane % E) == e ? v : sv;
-    }
+  for (int e = 1; e < E; ++e) {
+    const double v = bperm_f64(zr[e], src);
+    sv = (lane % E) == e ? v : sv;
   }
   s = sv;
   {
@@ -487,8 +521,11 @@ __device__ __forceinline__ void interface_solve(const double (&eA)[NT / kWave],
 // of every chunk is an interface unknown s_t; each thread eliminates its
 // remaining rows by Thomas' algorithm into x_j = y_j + g_j s_t + k_j s_{t+1}
 // (two spike columns), the interface rows form a periodic tridiagonal system
-// of NT unknowns solved by interface_solve() behind one barrier, and the
-// chunk is recombined.  row(j, a, b, c) returns the coefficients of local
+// of NT unknowns, solved behind one barrier by a few sweeps of every wavefront
+// over its own unknowns and its neighbours' ends, or by interface_solve()
+// where the couplings are too strong for that, and the chunk is recombined.
+// (The sweeps take about 85 vector instructions and 400 clocks from the
+// barrier on, the whole system solved by every wavefront 180 and 1800.)  row(j, a, b, c) returns the coefficients of local
 // slot j and d(j) its right-hand side (both evaluated once per slot).  xl and
 // xr receive the solution at the row before the chunk and the row after it
 // (the halo of x, from the interface values, without another exchange).
@@ -589,51 +626,93 @@ __device__ __forceinline__ void cyclic_solve(RowF row, DF d, double (&x)[PMAX], 
     ypl = lane == 0 ? wy : ypl;
     gpl = lane == 0 ? wg : gpl;
     kpl = lane == 0 ? wk : kpl;
-    const double eA[1] = {a0 * gpl}, eB[1] = {fma(a0, kpl, Bp)}, eC[1] = {C},
-                 eR[1] = {fma(-a0, ypl, Rp)};
-    interface_solve<NT>(eA, eB, eC, eR, t, s, snext, sprev, grow);
+    s = interface_wave(a0 * gpl, fma(a0, kpl, Bp), C, fma(-a0, ypl, Rp), lane);
+    snext = wave_next(s);
+    sprev = wave_prev(s);
   } else {
     // the equation of each wavefront's first chunk goes to LDS without its
     // left-tail terms (A holds a0); the reader completes it from L.etail
     const int w = t / kWave;
     const bool firstlane = lane == 0;
+    double A = firstlane ? a0 : a0 * gpl, B = firstlane ? Bp : fma(a0, kpl, Bp),
+           R = firstlane ? Rp : fma(-a0, ypl, Rp);
     const int pt = eq_pos<NT>(t);
-    L.eq[0][pt] = firstlane ? a0 : a0 * gpl;
-    L.eq[1][pt] = firstlane ? Bp : fma(a0, kpl, Bp);
+    L.eq[0][pt] = A;
+    L.eq[1][pt] = B;
     L.eq[2][pt] = C;
-    L.eq[3][pt] = firstlane ? Rp : fma(-a0, ypl, Rp);
+    L.eq[3][pt] = R;
     if (lane == kWave - 1) {
       L.etail[0][w] = yL;
       L.etail[1][w] = gL;
       L.etail[2][w] = kL;
     }
     __syncthreads();
-    {
-      const int wp = (w + W - 1) & (W - 1);
-      const double ty = L.etail[0][wp], tg = L.etail[1][wp], tk = L.etail[2][wp];
-      ypl = firstlane ? ty : ypl;
-      gpl = firstlane ? tg : gpl;
-      kpl = firstlane ? tk : kpl;
+    // Each wavefront sweeps its own equations and, as a second value per lane,
+    // those of its neighbours' ends: lanes 32..63 hold the wavefront before,
+    // lanes 0..31 the one after, so the neighbours of lanes 0 and 63 are the
+    // other value's lanes 63 and 0, and K sweeps are right as far as 31 - K
+    // lanes out.
+    const int wp = (w + W - 1) & (W - 1);
+    const int pg = eq_pos<NT>((t + (lane < 32 ? kWave : NT - kWave)) & (NT - 1));
+    double gA = L.eq[0][pg], gB = L.eq[1][pg], gR = L.eq[3][pg];
+    const double gC = L.eq[2][pg];
+    if (firstlane) {
+      ypl = L.etail[0][wp];
+      gpl = L.etail[1][wp];
+      kpl = L.etail[2][wp];
+      B = fma(A, kpl, B);
+      R = fma(-A, ypl, R);
+      A *= gpl;
+      gB = fma(gA, L.etail[2][w], gB);
+      gR = fma(-gA, L.etail[0][w], gR);
+      gA *= L.etail[1][w];
     }
-    double eA[W], eB[W], eC[W], eR[W];
+    const double inv = rcp64(B), ginv = rcp64(gB);
+    const double a = A * inv, c = C * inv, z = R * inv;
+    const double ga = gA * ginv, gc = gC * ginv, gz = gR * ginv;
+    const double e = vmax(fabs(a) + fabs(c), fabs(ga) + fabs(gc));
+    if (!__any(!(e <= kSweep6))) {
+      int k = __any(!(e <= kSweep2)) ? (__any(!(e <= kSweep4)) ? 6 : 4) : 2;
+      double gs = gz;
+      s = z;
+      auto around = [&] {  // the values before and after, of s and of gs
+        const double p = wave_prev(s), q = wave_prev(gs), u = wave_next(s), v = wave_next(gs);
+        const bool f = lane == 0, l = lane == kWave - 1;
+        sprev = f ? q : p;
+        snext = l ? v : u;
+        return SweepEnds{f ? p : q, l ? u : v};
+      };
+#pragma unroll 1
+      for (; k > 0; k -= 2) {
 #pragma unroll
-    for (int e = 0; e < W; ++e) {
-      eA[e] = L.eq[0][e * 65 + lane];
-      eB[e] = L.eq[1][e * 65 + lane];
-      eC[e] = L.eq[2][e * 65 + lane];
-      eR[e] = L.eq[3][e * 65 + lane];
+        for (int i = 0; i < 2; ++i) {
+          const SweepEnds g = around();
+          s = fma(-a, sprev, fma(-c, snext, z));
+          gs = fma(-ga, g.prev, fma(-gc, g.next, gz));
+        }
+      }
+      (void)around();
+    } else {
+      double eA[W], eB[W], eC[W], eR[W];
+#pragma unroll
+      for (int e2 = 0; e2 < W; ++e2) {
+        eA[e2] = L.eq[0][e2 * 65 + lane];
+        eB[e2] = L.eq[1][e2 * 65 + lane];
+        eC[e2] = L.eq[2][e2 * 65 + lane];
+        eR[e2] = L.eq[3][e2 * 65 + lane];
+      }
+      {
+        // equation W*lane is the first of a wavefront when (W*lane) % 64 == 0
+        const int wq = ((W * lane) / kWave + W - 1) & (W - 1);
+        const double ty = L.etail[0][wq], tg = L.etail[1][wq], tk = L.etail[2][wq];
+        const bool first = ((W * lane) & (kWave - 1)) == 0;
+        const double a1 = eA[0];
+        eA[0] = first ? a1 * tg : eA[0];
+        eB[0] = first ? fma(a1, tk, eB[0]) : eB[0];
+        eR[0] = first ? fma(-a1, ty, eR[0]) : eR[0];
+      }
+      interface_solve<NT>(eA, eB, eC, eR, t, s, snext, sprev, grow);
     }
-    {
-      // equation W*lane is the first of a wavefront when (W*lane) % 64 == 0
-      const int wq = ((W * lane) / kWave + W - 1) & (W - 1);
-      const double ty = L.etail[0][wq], tg = L.etail[1][wq], tk = L.etail[2][wq];
-      const bool first = ((W * lane) & (kWave - 1)) == 0;
-      const double a = eA[0];
-      eA[0] = first ? a * tg : eA[0];
-      eB[0] = first ? fma(a, tk, eB[0]) : eB[0];
-      eR[0] = first ? fma(-a, ty, eR[0]) : eR[0];
-    }
-    interface_solve<NT>(eA, eB, eC, eR, t, s, snext, sprev, grow);
   }
   // last row of chunk t-1: y + g s_{t-1} + k s_t with its tail values
   xl = fma(kpl, s, fma(gpl, sprev, ypl));

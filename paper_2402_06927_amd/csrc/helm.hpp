@@ -108,17 +108,13 @@ __device__ __forceinline__ void solve_helm(const HelmConst& K, const double (&ta
   const double r = K.r;
   // carries out of the chunk: the local forward scan at its last node and
   // the local backward scan at its first node
-  double fc = 0.0, bc = 0.0;
+  double fc = f[0], bc = FULL ? f[PMAX - 1] : 0.0;
 #pragma unroll
-  for (int j = 0; j < PMAX; ++j) fc = slot_live<PMAX, FULL>(j, cnt) ? fma(r, fc, f[j]) : fc;
+  for (int j = 1; j < PMAX; ++j) fc = slot_live<PMAX, FULL>(j, cnt) ? fma(r, fc, f[j]) : fc;
 #pragma unroll
-  for (int j = PMAX - 1; j >= 0; --j) bc = slot_live<PMAX, FULL>(j, cnt) ? fma(r, bc, f[j]) : bc;
+  for (int j = FULL ? PMAX - 2 : PMAX - 1; j >= 0; --j) bc = slot_live<PMAX, FULL>(j, cnt) ? fma(r, bc, f[j]) : bc;
   uint32_t word = 0;
-  double scale = 0.0;
-  if constexpr (RED) {
-    word = wave_max_word(R.diff);
-    if (R.first) scale = wave_max(R.scale);
-  }
+  if constexpr (RED) word = wave_max_word(R.diff);
   // inclusive scans over the wavefront, then the exclusive carries (xf*, xb*)
   double xfm, xfc, xbm, xbc, tm;
   if constexpr (FULL) {
@@ -186,6 +182,8 @@ __device__ __forceinline__ void solve_helm(const HelmConst& K, const double (&ta
     word = fabs(fc) <= 1.7976931348623157e308 ? word : kNonfinite;
     if (__any(R.bad)) word = kUnstable;
   }
+  double scale = 0.0;
+  if (RED && R.first) scale = wave_max(R.scale);
   // carries into the wavefront: the periodic sums over all wavefronts' totals,
   // farthest (its own) first, over 1 - r^N
   double cf, cb;
@@ -224,7 +222,7 @@ __device__ __forceinline__ void solve_helm(const HelmConst& K, const double (&ta
       if (R.first) {
         R.scale = L.hscale[slot][0];
 #pragma unroll
-        for (int i = 1; i < W; ++i) R.scale = fmax(R.scale, L.hscale[slot][i]);
+        for (int i = 1; i < W; ++i) R.scale = vmax(R.scale, L.hscale[slot][i]);
       }
     }
     cf = rf[0];

@@ -61,7 +61,8 @@ struct Parity {
 };
 
 // Two per-node arrays of the window (the explicit part of dv and the previous
-// Picard iterate) live in LDS as [slot][thread] when they fit next to the
+// Picard iterate) live in LDS, a thread's slots in pairs (an LDS read of 16
+// bytes a lane moves twice what two of 8 do in its time), when they fit next to the
 // solver's LDS (128 KiB for both: a workgroup may hold up to 160 KiB); when
 // only one fits, the explicit part goes to LDS and the iterate stays in
 // registers; otherwise both do.
@@ -70,12 +71,14 @@ struct AuxLds {
   static constexpr size_t kBytes = static_cast<size_t>(PMAX) * NT * sizeof(double);
   static constexpr bool kInLds = 2 * kBytes <= 131072;  // both arrays
   static constexpr bool kDInLds = kBytes <= 65536;     // the explicit part
-  double a[kInLds ? 2 : 1][kDInLds ? PMAX : 1][kDInLds ? NT : 1];
+  static_assert(kDInLds && PMAX % 2 == 0, "the explicit part is in LDS on every tile");
+  alignas(16) double a[kInLds ? 2 : 1][PMAX / 2][NT][2];
+  __device__ double& at(int s, int j, int t) { return a[s][j / 2][t][j % 2]; }
+  __device__ const double& at(int s, int j, int t) const { return a[s][j / 2][t][j % 2]; }
   // the explicit part's PMAX NT words, free from a step's last solve to the
   // next step's exchange (its readers have passed that solve's barriers)
   __device__ double* row0() {
-    static_assert(kDInLds, "the explicit part is in LDS on every tile");
-    return &a[0][0][0];
+    return &a[0][0][0][0];
   }
 };
 
@@ -305,7 +308,7 @@ template <int PMAX, int NT, bool FULL, bool KEEP = true, class NoiseF>
 __device__ int run_window(const StepParams& P, const HelmConst& K, NoiseF noise, int n_steps,
                           double (&m)[PMAX], double (&u)[PMAX], const Chunk& ch, RowLds<NT>& L,
                           AuxLds<PMAX, NT>& X, int t, Parity& par, int& iters) {
-  constexpr bool kLds = AuxLds<PMAX, NT>::kInLds, kDLds = AuxLds<PMAX, NT>::kDInLds;
+  constexpr bool kLds = AuxLds<PMAX, NT>::kInLds;
   const int cnt = ch.cnt;
   const double hdt = 0.5 * P.dt;
   // dv is carried as dv/4, the form in which it enters the rows of A (exact:
@@ -313,15 +316,15 @@ __device__ int run_window(const StepParams& P, const HelmConst& K, NoiseF noise,
   const double hdt4 = 0.25 * hdt;
   const double f1 = P.h / 3.0, f0 = 4.0 * P.h / 3.0;  // 2 M: (h/3, 4h/3, h/3)
   const bool bordered = FULL || K.base >= 2;
-  double rD[kDLds ? 1 : PMAX], rP[kLds ? 1 : PMAX];
+  double rP[kLds ? 1 : PMAX];
   // The thread's column of the LDS arrays.  It is laundered once per Picard
   // iteration, so the loads of the step's invariants are redone inside the
   // iteration (not hoisted into registers) and still issue back to back.
   int tx = t;
-  auto getD = [&](int j) -> double { if constexpr (kDLds) return X.a[0][j][tx]; else return rD[j]; };
-  auto setD = [&](int j, double v) { if constexpr (kDLds) X.a[0][j][tx] = v; else rD[j] = v; };
-  auto getP = [&](int j) -> double { if constexpr (kLds) return X.a[1][j][tx]; else return rP[j]; };
-  auto setP = [&](int j, double v) { if constexpr (kLds) X.a[1][j][tx] = v; else rP[j] = v; };
+  auto getD = [&](int j) -> double { return X.at(0, j, tx); };
+  auto setD = [&](int j, double v) { X.at(0, j, tx) = v; };
+  auto getP = [&](int j) -> double { if constexpr (kLds) return X.at(1, j, tx); else return rP[j]; };
+  auto setP = [&](int j, double v) { if constexpr (kLds) X.at(1, j, tx) = v; else rP[j] = v; };
   for (int n = 0; n < n_steps; ++n) {
     // (dU^n + dt/2 u^n) / 4 + o, the explicit part of dv / 4 + o
     double eL, eR, mL, mR, uL, uR;
@@ -436,14 +439,15 @@ __device__ int run_window(const StepParams& P, const HelmConst& K, NoiseF noise,
         break;
       }
       const double gdiff = __hiloint2double(static_cast<int>(R.word), 0);
-      const double gscale = R.scale;
-      if (k == 1) lim = P.tol * gscale;
+      if (k == 1) lim = P.tol * R.scale;
       // stop once the iterate's error is within tolerance: for a contraction
       // with ratio c, |m* - m_k| <= c / (1 - c) |m_k - m_{k-1}|; c is the ratio
       // of the last two changes, the bound is used while c < 1/2 (multiplied
       // out: d_k^2 <= lim (d_{k-1} - d_k)), the change itself otherwise
-      const bool done = (k > 1 && 2.0 * gdiff < gprev) ? gdiff * gdiff <= lim * (gprev - gdiff)
-                                                       : gdiff <= lim;
+      // (the same in every thread; __any makes the loop's exit a scalar branch)
+      const bool done = __any((k > 1 && 2.0 * gdiff < gprev)
+                                  ? gdiff * gdiff <= lim * (gprev - gdiff)
+                                  : gdiff <= lim);
       gprev = gdiff;
       if (done) {
         status = SCH_OK;
@@ -496,14 +500,14 @@ __device__ double block_nll(const double (&u)[PMAX], const Chunk& ch, int nx, in
   return 0.5 * block_sum<NT>(acc, L, t);
 }
 
-// Node e of a row staged in the auxiliary LDS array `slot` as [slot][j][t]
-// (the chunk layout of chunk_of: the first nx % NT threads hold one node more).
+// Node e of a row staged in the auxiliary LDS array `slot` slot by slot (the
+// chunk layout of chunk_of: the first nx % NT threads hold one node more).
 template <int PMAX, int NT>
 __device__ __forceinline__ double staged_at(const AuxLds<PMAX, NT>& X, int slot, int nx, int e) {
   const int base = nx / NT, rem = nx % NT, split = rem * (base + 1);
-  if (e < split) return X.a[slot][e % (base + 1)][e / (base + 1)];
+  if (e < split) return X.at(slot, e % (base + 1), e / (base + 1));
   const int f = e - split;
-  return X.a[slot][f % base][rem + f / base];
+  return X.at(slot, f % base, rem + f / base);
 }
 
 // The likelihood of block_nll with the velocity staged in auxiliary LDS
@@ -789,8 +793,8 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) k_
       // live through the likelihood and the copy-out
 #pragma unroll
       for (int jj = 0; jj < PMAX; ++jj) {
-        X.a[0][jj][t] = u[jj];
-        X.a[1][jj][t] = m[jj];
+        X.at(0, jj, t) = u[jj];
+        X.at(1, jj, t) = m[jj];
       }
       __syncthreads();
       phin = staged_nll<PMAX, NT>(X, nx, A.n_obs, A.y, A.sigma, L, t, girs);

@@ -1,0 +1,73 @@
+"""The chunks' interface system in each of its regimes: two, four and six sweeps,
+the whole system in every wavefront, and on one wavefront a particle the sweeps
+after no, one and several reduction levels.  The viscosity sets how far the
+couplings reach (a chunk of c nodes couples its ends by about r^c, r the root of
+the step matrix), so the same grids walk through the regimes.  Against the
+oracle's pivoted solve at the parity tolerance; a regime taken one step too
+early is off by its bound's square root and more."""
+import numpy as np
+import pytest
+
+import oracle as O
+import pairing as PR
+from paper_2402_06927_amd import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sch():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2402_06927_amd import sch as S
+
+    S.lib()
+    yield S
+    S.sch_tune_set(S.TUNE_THREADS, 0)
+
+
+def coupling(wl, threads):
+    """Largest |A| + |C| over |B| of the interface rows at dv = 0."""
+    h = wl.L / wl.nx
+    o, d = h / 6 - wl.mu * wl.dt / (2 * h), 2 * h / 3 + wl.mu * wl.dt / h
+    x = d / (2 * abs(o))
+    r = x - np.sqrt(x * x - 1)
+    return 2.0 / (r ** -(wl.nx // threads) + r ** (wl.nx // threads))
+
+
+CASES = [(nx, threads, mu)
+         for nx, threads in ((64, 64), (100, 64), (250, 64), (1000, 64), (1024, 64), (1024, 128),
+                             (2000, 128), (1100, 256), (2048, 256), (4096, 256), (3000, 512),
+                             (4096, 512), (8192, 512))
+         for mu in (0.0, 0.01, 0.03, 0.2, 1.0, 10.0)]
+
+
+@pytest.mark.parametrize("nx,threads,mu", CASES)
+def test_window_across_coupling_regimes(sch, nx, threads, mu):
+    n, s, q = 2, 2, 3
+    wl = W.BOOTSTRAP_256.scaled(nx=nx, n_modes=q, n_steps=s, mu=mu)
+    print("interface", nx, threads, mu, "coupling %.1e" % coupling(wl, threads), flush=True)
+    om, gm = PR.oracle_model(wl), PR.gpu_model(wl)
+    u0, m0, _, _ = PR.prior(wl, n)
+    dW = O.draw_increments(wl.seed, n, s, q, 0, O.TAG_FORECAST, 0, wl.dt)
+    worst, m_ref, u_ref, _, _ = O.ensemble_window(om, m0, u0, dW)
+    assert worst == 0
+    m, u, d = (torch.tensor(np.ascontiguousarray(a), device="cuda") for a in (m0, u0, dW))
+    status = torch.full((n,), 99, dtype=torch.int32, device="cuda")
+    sch.sch_tune_set(sch.TUNE_THREADS, threads)
+    sch.sch_ensemble_step(gm, m, u, d, None, status)
+    sch.sch_tune_set(sch.TUNE_THREADS, 0)
+    assert int(status.abs().max()) == 0
+    assert PR.rel_l2(m.cpu().numpy(), m_ref) < PR.REL_TOL
+    assert PR.rel_l2(u.cpu().numpy(), u_ref) < PR.REL_TOL
+
+
+def test_cases_reach_every_regime():
+    from collections import Counter
+
+    seen = Counter()
+    for nx, threads, mu in CASES:
+        e = coupling(W.BOOTSTRAP_256.scaled(nx=nx, mu=mu), threads)
+        seen[threads > 64, 2 if e <= 2.0 ** -19 else 4 if e <= 3.4e-4 else 6 if e <= 3.4e-3 else 0] += 1
+    assert all(seen[True, k] for k in (0, 2, 4, 6)) and all(seen[False, k] for k in (0, 2, 4)), seen
