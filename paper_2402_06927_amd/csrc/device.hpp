@@ -189,11 +189,7 @@ __device__ __forceinline__ int wave_or(int v) {
 template <int NT>
 struct RowLds {
   static constexpr int W = NT / kWave;
-  // interface equations (A, B, C, R), one per chunk, equation t at
-  // eq_pos(t) = (t % W) * 65 + t / W: a lane's W consecutive equations lie
-  // 65 words apart, so both the writes (one per thread) and the reads (W per
-  // lane) touch consecutive banks
-  double eq[4][65 * W];
+  alignas(16) double eq[4][NT];  // interface equations (A, B, C, R), one per chunk
   double etail[3][W];          // last-row spike values of each wavefront's last chunk
   double edge[2][W][6];        // wavefront edge values of halo exchanges, double buffered
   double red[3][W];            // workgroup reductions
@@ -208,12 +204,6 @@ struct RowLds {
   // [1] the Matern-type noise's
   double tab[2][3][kWave];
 };
-
-template <int NT>
-__device__ __forceinline__ int eq_pos(int t) {
-  constexpr int W = NT / kWave;
-  return (t % W) * 65 + t / W;
-}
 
 // 1/x for the solvers' pivots: the hardware estimate (relative error about
 // 5e-8 on gfx950) and one Newton step, which squares that error (at most
@@ -388,10 +378,15 @@ __device__ __forceinline__ void spike_eliminate(const double (&A)[E], const doub
 // eps |B|, K sweeps s <- (R - A s_prev - C s_next) / B from s = R / B leave an
 // error below eps^(K+1) of the largest unknown; these bounds give 2^-57, a
 // sixteenth of the rounding of the result.
-struct SweepEnds {
-  double prev, next;
-};
 constexpr double kSweep2 = 0x1.0p-19, kSweep4 = 3.4e-4, kSweep6 = 3.4e-3;
+// Sweeps that the wavefront's equations s + a s_prev + c s_next = z take; 0 if
+// six are not enough.
+__device__ __forceinline__ int sweeps_for(double a, double c) {
+  const double e = fabs(a) + fabs(c);
+  if (!__any(!(e <= kSweep2))) return 2;
+  if (!__any(!(e <= kSweep4))) return 4;
+  return __any(!(e <= kSweep6)) ? 0 : 6;
+}
 
 // The same system over the 64 lanes of one wavefront, lane l holding equation
 // l (periodic): sweeps where they suffice, cyclic reduction levels (which
@@ -522,13 +517,12 @@ __device__ __forceinline__ void interface_solve(const double (&eA)[NT / kWave],
 // remaining rows by Thomas' algorithm into x_j = y_j + g_j s_t + k_j s_{t+1}
 // (two spike columns), the interface rows form a periodic tridiagonal system
 // of NT unknowns, solved behind one barrier by a few sweeps of every wavefront
-// over its own unknowns and its neighbours' ends, or by interface_solve()
-// where the couplings are too strong for that, and the chunk is recombined.
-// (The sweeps take about 85 vector instructions and 400 clocks from the
-// barrier on, the whole system solved by every wavefront 180 and 1800.)  row(j, a, b, c) returns the coefficients of local
-// slot j and d(j) its right-hand side (both evaluated once per slot).  xl and
-// xr receive the solution at the row before the chunk and the row after it
-// (the halo of x, from the interface values, without another exchange).
+// over its own unknowns and its neighbours' halves, or by interface_solve()
+// where the couplings are too strong for that (above about 0.2), and the chunk
+// is recombined.  row(j, a, b, c) returns the coefficients of local slot j and
+// d(j) its right-hand side (both evaluated once per slot).  xl and xr receive
+// the solution at the row before the chunk and the row after it (the halo of
+// x, from the interface values, without another exchange).
 //
 // No pivoting.  The mass and Helmholtz matrices are symmetric positive
 // definite and diagonally dominant.  A row of the implicit-midpoint matrix,
@@ -634,84 +628,106 @@ __device__ __forceinline__ void cyclic_solve(RowF row, DF d, double (&x)[PMAX], 
     // left-tail terms (A holds a0); the reader completes it from L.etail
     const int w = t / kWave;
     const bool firstlane = lane == 0;
-    double A = firstlane ? a0 : a0 * gpl, B = firstlane ? Bp : fma(a0, kpl, Bp),
-           R = firstlane ? Rp : fma(-a0, ypl, Rp);
-    const int pt = eq_pos<NT>(t);
-    L.eq[0][pt] = A;
-    L.eq[1][pt] = B;
-    L.eq[2][pt] = C;
-    L.eq[3][pt] = R;
+    L.eq[0][t] = firstlane ? a0 : a0 * gpl;
+    L.eq[1][t] = firstlane ? Bp : fma(a0, kpl, Bp);
+    L.eq[2][t] = C;
+    L.eq[3][t] = firstlane ? Rp : fma(-a0, ypl, Rp);
     if (lane == kWave - 1) {
       L.etail[0][w] = yL;
       L.etail[1][w] = gL;
       L.etail[2][w] = kL;
     }
     __syncthreads();
-    // Each wavefront sweeps its own equations and, as a second value per lane,
-    // those of its neighbours' ends: lanes 32..63 hold the wavefront before,
-    // lanes 0..31 the one after, so the neighbours of lanes 0 and 63 are the
-    // other value's lanes 63 and 0, and K sweeps are right as far as 31 - K
-    // lanes out.
+    // Each wavefront takes its own equations and 32 on either side, lane l the
+    // two from 64 w - 32 + 2 l on (with two wavefronts that is the whole
+    // ring).  The odd ones are eliminated, which squares the couplings, and
+    // the 64 even ones swept; what is wrong at the window's ends stays out of
+    // the sweeps' reach of the unknowns taken (lanes 15..48).
+    typedef double d2 __attribute__((ext_vector_type(2)));
     const int wp = (w + W - 1) & (W - 1);
-    const int pg = eq_pos<NT>((t + (lane < 32 ? kWave : NT - kWave)) & (NT - 1));
-    double gA = L.eq[0][pg], gB = L.eq[1][pg], gR = L.eq[3][pg];
-    const double gC = L.eq[2][pg];
-    if (firstlane) {
-      ypl = L.etail[0][wp];
-      gpl = L.etail[1][wp];
-      kpl = L.etail[2][wp];
-      B = fma(A, kpl, B);
-      R = fma(-A, ypl, R);
-      A *= gpl;
-      gB = fma(gA, L.etail[2][w], gB);
-      gR = fma(-gA, L.etail[0][w], gR);
-      gA *= L.etail[1][w];
-    }
-    const double inv = rcp64(B), ginv = rcp64(gB);
-    const double a = A * inv, c = C * inv, z = R * inv;
-    const double ga = gA * ginv, gc = gC * ginv, gz = gR * ginv;
-    const double e = vmax(fabs(a) + fabs(c), fabs(ga) + fabs(gc));
-    if (!__any(!(e <= kSweep6))) {
-      int k = __any(!(e <= kSweep2)) ? (__any(!(e <= kSweep4)) ? 6 : 4) : 2;
-      double gs = gz;
-      s = z;
-      auto around = [&] {  // the values before and after, of s and of gs
-        const double p = wave_prev(s), q = wave_prev(gs), u = wave_next(s), v = wave_next(gs);
-        const bool f = lane == 0, l = lane == kWave - 1;
-        sprev = f ? q : p;
-        snext = l ? v : u;
-        return SweepEnds{f ? p : q, l ? u : v};
-      };
-#pragma unroll 1
-      for (; k > 0; k -= 2) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          const SweepEnds g = around();
-          s = fma(-a, sprev, fma(-c, snext, z));
-          gs = fma(-ga, g.prev, fma(-gc, g.next, gz));
-        }
+    const int n0 = (kWave * w + NT - 32 + 2 * lane) & (NT - 1);
+    d2 eA = *reinterpret_cast<const d2*>(&L.eq[0][n0]), eB = *reinterpret_cast<const d2*>(&L.eq[1][n0]);
+    const d2 eC = *reinterpret_cast<const d2*>(&L.eq[2][n0]);
+    d2 eR = *reinterpret_cast<const d2*>(&L.eq[3][n0]);
+    {
+      const int q = lane < 32 ? wp : w;
+      const double ty = L.etail[0][q], tg = L.etail[1][q], tk = L.etail[2][q];
+      if ((lane & 31) == 16) {  // the first equations of this wavefront and the next
+        eB.x = fma(eA.x, tk, eB.x);
+        eR.x = fma(-eA.x, ty, eR.x);
+        eA.x *= tg;
       }
-      (void)around();
-    } else {
-      double eA[W], eB[W], eC[W], eR[W];
+      if (firstlane) {
+        ypl = ty;
+        gpl = tg;
+        kpl = tk;
+      }
+    }
+    const double i1 = rcp64(eB.y), y = eR.y * i1, g1 = -eA.y * i1, k1 = -eC.y * i1;
+    grow = vmax_abs(grow, k1);
+    double a, c, z;
+    {
+      const double py = wave_prev(y), pg = wave_prev(g1), pk = wave_prev(k1);
+      const double inv = rcp64(fma(eA.x, pk, fma(eC.x, g1, eB.x)));
+      a = eA.x * pg * inv;
+      c = eC.x * k1 * inv;
+      z = fma(-eA.x, py, fma(-eC.x, y, eR.x)) * inv;
+    }
+    double v = z;
+    int sweeps = sweeps_for(a, c);
+    bool swept = sweeps != 0;
+    if (swept) {
+#pragma unroll 1
+      for (; sweeps > 0; sweeps -= 2) {
 #pragma unroll
-      for (int e2 = 0; e2 < W; ++e2) {
-        eA[e2] = L.eq[0][e2 * 65 + lane];
-        eB[e2] = L.eq[1][e2 * 65 + lane];
-        eC[e2] = L.eq[2][e2 * 65 + lane];
-        eR[e2] = L.eq[3][e2 * 65 + lane];
+        for (int i = 0; i < 2; ++i) v = fma(-a, wave_prev(v), fma(-c, wave_next(v), z));
+      }
+    } else {
+      // one level of cyclic reduction: the couplings squared again, to the
+      // lanes two away
+      const double am = wave_prev(a), cm = wave_prev(c), zm = wave_prev(z);
+      const double ap = wave_next(a), cpn = wave_next(c), zp = wave_next(z);
+      const double inv = rcp64(fma(-a, cm, fma(-c, ap, 1.0)));
+      z = fma(-a, zm, fma(-c, zp, z)) * inv;
+      a = -a * am * inv;
+      c = -c * cpn * inv;
+      v = z;
+      sweeps = sweeps_for(a, c);
+      swept = sweeps != 0;
+#pragma unroll 1
+      for (; sweeps > 0; --sweeps)
+        v = fma(-a, wave_prev(wave_prev(v)), fma(-c, wave_next(wave_next(v)), z));
+    }
+    if (swept) {
+      const double o = fma(k1, wave_next(v), fma(g1, v, y));  // the odd unknowns
+      const int src = 16 + lane / 2;
+      const double se = bperm_f64(v, src), so = bperm_f64(o, src);
+      s = (lane & 1) ? so : se;
+      const double sl = readlane_f64(o, 15), sr = readlane_f64(v, 48);
+      sprev = wave_prev(s);
+      snext = wave_next(s);
+      sprev = firstlane ? sl : sprev;
+      snext = lane == kWave - 1 ? sr : snext;
+    } else {
+      double fA[W], fB[W], fC[W], fR[W];
+#pragma unroll
+      for (int e = 0; e < W; ++e) {
+        fA[e] = L.eq[0][W * lane + e];
+        fB[e] = L.eq[1][W * lane + e];
+        fC[e] = L.eq[2][W * lane + e];
+        fR[e] = L.eq[3][W * lane + e];
       }
       {
         // equation W*lane is the first of a wavefront when (W*lane) % 64 == 0
         const int wq = ((W * lane) / kWave + W - 1) & (W - 1);
         const double ty = L.etail[0][wq], tg = L.etail[1][wq], tk = L.etail[2][wq];
         const bool first = ((W * lane) & (kWave - 1)) == 0;
-        const double a1 = eA[0];
-        eA[0] = first ? a1 * tg : eA[0];
-        eB[0] = first ? fma(a1, tk, eB[0]) : eB[0];
-        eR[0] = first ? fma(-a1, ty, eR[0]) : eR[0];
+        const double a1 = fA[0];
+        fA[0] = first ? a1 * tg : fA[0];
+        fB[0] = first ? fma(a1, tk, fB[0]) : fB[0];
+        fR[0] = first ? fma(-a1, ty, fR[0]) : fR[0];
       }
-      interface_solve<NT>(eA, eB, eC, eR, t, s, snext, sprev, grow);
+      interface_solve<NT>(fA, fB, fC, fR, t, s, snext, sprev, grow);
     }
   }
   // last row of chunk t-1: y + g s_{t-1} + k s_t with its tail values

@@ -1,6 +1,7 @@
-"""The chunks' interface system in each of its regimes: two, four and six sweeps,
-the whole system in every wavefront, and on one wavefront a particle the sweeps
-after no, one and several reduction levels.  The viscosity sets how far the
+"""The chunks' interface system in each of its regimes: two, four and six sweeps
+of the even unknowns, the same after a reduction level, the whole system in
+every wavefront, and on one wavefront a particle the sweeps after no, one and
+several reduction levels.  The viscosity sets how far the
 couplings reach (a chunk of c nodes couples its ends by about r^c, r the root of
 the step matrix), so the same grids walk through the regimes.  Against the
 oracle's pivoted solve at the parity tolerance; a regime taken one step too
@@ -66,8 +67,23 @@ def test_window_across_coupling_regimes(sch, nx, threads, mu):
 def test_cases_reach_every_regime():
     from collections import Counter
 
-    seen = Counter()
+    def halve(e):  # couplings after every other unknown is eliminated
+        return e * e / 2 / (1 - e * e / 2)
+
+    def sweeps(e):
+        return 2 if e <= 2.0 ** -19 else 4 if e <= 3.4e-4 else 6 if e <= 3.4e-3 else 0
+
+    one, several = Counter(), Counter()
     for nx, threads, mu in CASES:
         e = coupling(W.BOOTSTRAP_256.scaled(nx=nx, mu=mu), threads)
-        seen[threads > 64, 2 if e <= 2.0 ** -19 else 4 if e <= 3.4e-4 else 6 if e <= 3.4e-3 else 0] += 1
-    assert all(seen[True, k] for k in (0, 2, 4, 6)) and all(seen[False, k] for k in (0, 2, 4)), seen
+        if threads == 64:
+            levels = 0
+            while e > 3.4e-4 and levels < 6:
+                e, levels = halve(e), levels + 1
+            one[min(levels, 2), sweeps(e)] += 1
+        else:
+            e = halve(e)
+            several[("", e and sweeps(e)) if sweeps(e) else ("level", sweeps(halve(e)))] += 1
+    assert all(several["", k] for k in (2, 4, 6)) and several["level", 0], several
+    assert any(several["level", k] for k in (2, 4, 6)), several
+    assert all(any(one[n, k] for k in (2, 4)) for n in (0, 1, 2)), one
