@@ -282,11 +282,10 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) k_
     if constexpr (MATERN) {
       return [&, n](int, double (&e)[PMAX]) {
         if (n >= CS || (!dW && !dL)) return;
-        double w[PMAX];
-#pragma unroll
-        for (int j = 0; j < PMAX; ++j)
-          w[j] = slot_live<PMAX, FULL>(j, ch.cnt) ? incv(n, ch.start + j) : 0.0;
-        matern_add<PMAX, NT, FULL>(A.M, w, e, ch, L, t, par);
+        auto pair = [&](int n2, int i, bool both) {
+          return pair_t{incv(n2, i), both ? incv(n2, i + 1) : 0.0};
+        };
+        matern_noise<PMAX, NT, FULL, true>(A.M, pair, n, e, ch, X.row0(), L, t, nx, par);
       };
     } else {
       // (the reverse sweep keeps values of its own in the staging row: FENCE)

@@ -29,13 +29,14 @@ __device__ __forceinline__ Ctr4 philox10(Ctr4 c, uint64_t seed) {
   uint32_t ka = static_cast<uint32_t>(seed), kb = static_cast<uint32_t>(seed >> 32);
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
-    const uint32_t hiA = __umulhi(kMulA, c.w[0]), loA = kMulA * c.w[0];
-    const uint32_t hiB = __umulhi(kMulB, c.w[2]), loB = kMulB * c.w[2];
+    // both halves of a product from one multiplication
+    const uint64_t a = static_cast<uint64_t>(kMulA) * c.w[0];
+    const uint64_t b = static_cast<uint64_t>(kMulB) * c.w[2];
     Ctr4 n;
-    n.w[0] = hiB ^ c.w[1] ^ ka;
-    n.w[1] = loB;
-    n.w[2] = hiA ^ c.w[3] ^ kb;
-    n.w[3] = loA;
+    n.w[0] = static_cast<uint32_t>(b >> 32) ^ c.w[1] ^ ka;
+    n.w[1] = static_cast<uint32_t>(b);
+    n.w[2] = static_cast<uint32_t>(a >> 32) ^ c.w[3] ^ kb;
+    n.w[3] = static_cast<uint32_t>(a);
     c = n;
     ka += kWeylA;
     kb += kWeylB;
@@ -45,20 +46,100 @@ __device__ __forceinline__ Ctr4 philox10(Ctr4 c, uint64_t seed) {
 
 // 53 high bits of (hi:lo) as an exact double in [0, 1).
 __device__ __forceinline__ double unit_double(uint32_t hi, uint32_t lo) {
-  const uint64_t bits = (static_cast<uint64_t>(hi) << 32) | lo;
-  return static_cast<double>(bits >> 11) * 0x1.0p-53;
+  return fma(static_cast<double>(hi), 0x1.0p-32, static_cast<double>(lo >> 11) * 0x1.0p-53);
+}
+
+// 1/x: the hardware estimate (relative error about 5e-8 on gfx950) and one
+// Newton step, which squares that error (at most about 11 ulp, 2e-15
+// relative).
+__device__ __forceinline__ double rcp64(double x) {
+  const double r = __builtin_amdgcn_rcp(x);
+  return fma(r, fma(-x, r, 1.0), r);
+}
+
+// The two factors of a Box-Muller pair.  The device library's log, sqrt and
+// sincos cover all arguments (330 instructions a pair, with branches for
+// reductions that never happen here); these cover the ones that do, from the
+// plain series, in about 95.  Together with the single multiplication of
+// philox10 they took the jitter with the Matern-type noise, which draws a pair
+// for every two nodes, steps and moves, from 18.4 to 17.4 ms at 4096 nodes and
+// 1024 particles.
+//
+// sqrt(-2 log v) for v = k 2^-53 in (0, 1].  v = 2^e m with m in [0.707, 1.414),
+// log m = 2 atanh(s), s = (m - 1) / (m + 1), |s| <= 0.172: the series to s^19
+// is cut off at 3e-17 of it.
+__device__ __forceinline__ double box_radius(double v) {
+  double m = __builtin_amdgcn_frexp_mant(v);  // [0.5, 1)
+  int e = __builtin_amdgcn_frexp_exp(v);
+  const bool low = m < 0.70710678118654752;
+  m = low ? m + m : m;
+  e = low ? e - 1 : e;
+  const double f = m - 1.0, d = 2.0 + f, r = rcp64(d);
+  double s = f * r;
+  s = fma(fma(-s, d, f), r, s);
+  const double z = s * s;
+  double p = 1.0 / 19.0;
+  p = fma(p, z, 1.0 / 17.0);
+  p = fma(p, z, 1.0 / 15.0);
+  p = fma(p, z, 1.0 / 13.0);
+  p = fma(p, z, 1.0 / 11.0);
+  p = fma(p, z, 1.0 / 9.0);
+  p = fma(p, z, 1.0 / 7.0);
+  p = fma(p, z, 1.0 / 5.0);
+  p = fma(p, z, 1.0 / 3.0);
+  // ln 2 in two parts, the first with 20 trailing zero bits: its products with
+  // the exponent (at most 53) are exact
+  constexpr double kLn2Hi = 0x1.62e42feep-1, kLn2Lo = 0x1.a39ef35793c76p-33;
+  const double k = static_cast<double>(e);
+  const double l = fma(k, kLn2Hi, fma(2.0, s, fma(2.0 * s * z, p, k * kLn2Lo)));
+  // sqrt(x) by the coupled iteration for sqrt and its half reciprocal; x = 0
+  // (v = 1) has no reciprocal
+  const double x = -2.0 * l, y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  const double q = fma(-h, g, 0.5);
+  g = fma(g, q, g);
+  h = fma(h, q, h);
+  g = fma(fma(-g, g, x), h, g);
+  return v < 1.0 ? g : 0.0;
+}
+
+// sin and cos of 2 pi u for u = k 2^-53 in [0, 1): the nearest quarter turn is
+// taken off exactly, and |2 pi r| <= pi / 4 goes into the Taylor polynomials to
+// the 17th and 16th power (cut off at 6e-20 and 2e-18).
+__device__ __forceinline__ void turn_sincos(double u, double& sn, double& cs) {
+  const double qd = rint(4.0 * u);
+  const int n = static_cast<int>(qd);
+  const double x = 6.283185307179586 * fma(-0.25, qd, u), w = x * x;
+  double a = 1.0 / 355687428096000.0;
+  a = fma(a, w, -1.0 / 1307674368000.0);
+  a = fma(a, w, 1.0 / 6227020800.0);
+  a = fma(a, w, -1.0 / 39916800.0);
+  a = fma(a, w, 1.0 / 362880.0);
+  a = fma(a, w, -1.0 / 5040.0);
+  a = fma(a, w, 1.0 / 120.0);
+  a = fma(a, w, -1.0 / 6.0);
+  const double s = fma(x * w, a, x);
+  double b = 1.0 / 20922789888000.0;
+  b = fma(b, w, -1.0 / 87178291200.0);
+  b = fma(b, w, 1.0 / 479001600.0);
+  b = fma(b, w, -1.0 / 3628800.0);
+  b = fma(b, w, 1.0 / 40320.0);
+  b = fma(b, w, -1.0 / 720.0);
+  b = fma(b, w, 1.0 / 24.0);
+  const double c = fma(w * w, b, fma(-0.5, w, 1.0));
+  sn = (n & 1) ? c : s;
+  cs = (n & 1) ? s : c;
+  sn = (n & 2) ? -sn : sn;
+  cs = ((n + 1) & 2) ? -cs : cs;
 }
 
 // Two standard normals from one Philox block (Box-Muller on 1 - u1 in (0,1]).
 __device__ __forceinline__ void normal2(uint64_t seed, uint32_t c0, uint32_t c1, uint32_t c2,
                                         uint32_t c3, double& z0, double& z1) {
   const Ctr4 r = philox10(Ctr4{{c0, c1, c2, c3}}, seed);
-  const double u1 = unit_double(r.w[0], r.w[1]);
-  const double u2 = unit_double(r.w[2], r.w[3]);
-  const double rad = sqrt(-2.0 * log(1.0 - u1));
-  const double ang = 6.283185307179586 * u2;
+  const double rad = box_radius(1.0 - unit_double(r.w[0], r.w[1]));
   double sn, cs;
-  sincos(ang, &sn, &cs);
+  turn_sincos(unit_double(r.w[2], r.w[3]), sn, cs);
   z0 = rad * cs;
   z1 = rad * sn;
 }
@@ -204,16 +285,6 @@ struct RowLds {
   // [1] the Matern-type noise's
   double tab[2][3][kWave];
 };
-
-// 1/x for the solvers' pivots: the hardware estimate (relative error about
-// 5e-8 on gfx950) and one Newton step, which squares that error (at most
-// about 11 ulp, 2e-15 relative).  Small pivots are not excluded by the
-// matrices themselves: an elimination that meets them grows its eliminated
-// super-diagonal, which the solvers measure (kMaxGrowth below).
-__device__ __forceinline__ double rcp64(double x) {
-  const double r = __builtin_amdgcn_rcp(x);
-  return fma(r, fma(-x, r, 1.0), r);
-}
 
 // A row of the periodic mesh is split over the NT threads of a workgroup:
 // thread t owns the `cnt` consecutive rows starting at `start`, held in
@@ -524,6 +595,8 @@ __device__ __forceinline__ void interface_solve(const double (&eA)[NT / kWave],
 // the solution at the row before the chunk and the row after it (the halo of
 // x, from the interface values, without another exchange).
 //
+// The pivots' reciprocals (rcp64) do not exclude small ones: an elimination
+// that meets them grows its eliminated super-diagonal, which is measured.
 // No pivoting.  The mass and Helmholtz matrices are symmetric positive
 // definite and diagonally dominant.  A row of the implicit-midpoint matrix,
 // (o - v_-, d + v_+ - v_-, o + v_+) with o = h/6 - mu dt/(2h),

@@ -217,24 +217,17 @@ struct MaternDev {
   int k;
 };
 
-// Adds the Matern-type noise field of one step to e.  w holds the chunk's
-// cell increments Delta W_i (cell i = [x_i, x_{i+1}], held by the thread that
-// holds node i).  The load vector of Delta W_h is
-// b_i = eta sqrt(h) (Delta W_{i-1} + Delta W_i) / 2; then
-// (M + kappa^{-2} K) U_1 = b and (M + kappa^{-2} K) U_j = M U_{j-1}, each
-// solve in the scan form of solve_helm, the mass products with the bordering
-// values of the previous solve as halo (chunks of >= 2 rows) or an exchange.
+// Adds the Matern-type noise field of one step to e: from the load vector r,
+// (M + kappa^{-2} K) U_1 = r and (M + kappa^{-2} K) U_j = M U_{j-1}, each solve in
+// the scan form of solve_helm, the mass products with the bordering values of
+// the previous solve as halo (chunks of >= 2 rows) or an exchange.
 template <int PMAX, int NT, bool FULL>
-__device__ __forceinline__ void matern_add(const MaternDev& M, const double (&w)[PMAX],
-                                           double (&e)[PMAX], const Chunk& ch, RowLds<NT>& L,
-                                           int t, Parity& par) {
+__device__ __forceinline__ void matern_solves(const MaternDev& M, double (&r)[PMAX],
+                                              double (&e)[PMAX], const Chunk& ch, RowLds<NT>& L,
+                                              int t, Parity& par) {
   const int cnt = ch.cnt;
   const bool bordered = FULL || M.K.base >= 2;
-  double wl, wr;
-  halo<PMAX, NT, FULL>(w, cnt, L, t, wl, wr, par.hs);
-  double r[PMAX], U[PMAX];
-#pragma unroll
-  for (int j = 0; j < PMAX; ++j) r[j] = M.load * (left_of<PMAX, FULL>(w, j, wl) + w[j]);
+  double U[PMAX];
   double uL = 0.0, uR = 0.0;
   for (int i = 0; i < M.k; ++i) {
     if (i > 0) {
@@ -248,6 +241,59 @@ __device__ __forceinline__ void matern_add(const MaternDev& M, const double (&w)
 #pragma unroll
   for (int j = 0; j < PMAX; ++j)
     if (slot_live<PMAX, FULL>(j, cnt)) e[j] += U[j];
+}
+
+// The same from the chunk's cell increments Delta W_i (cell i = [x_i, x_{i+1}],
+// held by the thread that holds node i): the load vector of Delta W_h is
+// b_i = eta sqrt(h) (Delta W_{i-1} + Delta W_i) / 2.
+template <int PMAX, int NT, bool FULL>
+__device__ __forceinline__ void matern_add(const MaternDev& M, const double (&w)[PMAX],
+                                           double (&e)[PMAX], const Chunk& ch, RowLds<NT>& L,
+                                           int t, Parity& par) {
+  double wl, wr, r[PMAX];
+  halo<PMAX, NT, FULL>(w, ch.cnt, L, t, wl, wr, par.hs);
+#pragma unroll
+  for (int j = 0; j < PMAX; ++j) r[j] = M.load * (left_of<PMAX, FULL>(w, j, wl) + w[j]);
+  matern_solves<PMAX, NT, FULL>(M, r, e, ch, L, t, par);
+}
+
+// The same with the cells of step n produced in pairs, as the mode table is
+// summed (modes_noise: consecutive lanes on consecutive cells, 16 bytes each,
+// exchanged through LDS, where the cell left of the chunk is found too):
+// pair(n, i, both) gives the increments of cells i (even) and, if both, i + 1.
+// stg, FENCE: as for modes_noise.
+typedef double pair_t __attribute__((ext_vector_type(2)));
+typedef double pair8_t __attribute__((ext_vector_type(2), aligned(8)));  // rows of odd grids
+template <int PMAX, int NT, bool FULL, bool FENCE, class PairF>
+__device__ __forceinline__ void matern_noise(const MaternDev& M, PairF pair, int n,
+                                             double (&e)[PMAX], const Chunk& ch, double* stg,
+                                             RowLds<NT>& L, int t0, int nx, Parity& par) {
+  constexpr int H = PMAX / 2;
+  int t = t0;
+  Chunk own = ch;
+  asm volatile("" : "+v"(t), "+v"(own.start));
+  if (FENCE) __syncthreads();
+  const int p0 = stage_pos(2 * t);
+#pragma unroll 2
+  for (int k = 0; k < H; ++k) {
+    const int i = 2 * (t + NT * k);
+    if (FULL || i < nx) {
+      const pair_t w = pair(n, i, FULL || i + 1 < nx);
+      const int c = p0 ^ ((NT / 16 * k) & 15);
+      stg[2 * NT * k + c] = w.x;
+      stg[2 * NT * k + (c ^ 1)] = w.y;
+    }
+  }
+  __syncthreads();
+  double r[PMAX];
+  double left = stg[stage_pos(own.start > 0 ? own.start - 1 : nx - 1)];
+#pragma unroll
+  for (int j = 0; j < PMAX; ++j) {
+    const double w = staged_slot<PMAX, FULL>(stg, own, t, j);
+    r[j] = M.load * (left + w);
+    left = w;
+  }
+  matern_solves<PMAX, NT, FULL>(M, r, e, ch, L, t0, par);
 }
 
 // The transpose of the map of matern_add (cells Delta W -> field U_k): with
@@ -575,10 +621,13 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) k_
   if constexpr (MATERN) {
     const int nx = A.P.nx;
     const double* cells = A.dW + static_cast<size_t>(p) * A.n_steps * nx;
+    auto pair = [&](int n, int i, bool both) {
+      const double* c = cells + static_cast<size_t>(n) * nx + i;
+      if (both) return pair_t(*reinterpret_cast<const pair8_t*>(c));
+      return pair_t{*c, 0.0};
+    };
     auto noise = [&](int n, double (&e)[PMAX]) {
-      double w[PMAX];
-      load_chunk<PMAX, FULL>(cells + static_cast<size_t>(n) * nx, ch, w);
-      matern_add<PMAX, NT, FULL>(A.M, w, e, ch, L, t, par);
+      matern_noise<PMAX, NT, FULL, false>(A.M, pair, n, e, ch, X.row0(), L, t, nx, par);
     };
     st = run_window<PMAX, NT, FULL, true>(A.P, K, noise, A.n_steps, m, u, ch, L, X, t, par,
                                                 iters);
@@ -674,19 +723,6 @@ __device__ __forceinline__ void cell_normals(uint64_t seed, uint32_t c0, uint32_
   }
 }
 
-// pCN proposal for the chunk's cells of one step (section 3.1.2):
-// w_i = rho c_i + sqrt(1 - rho^2) sqrt(dt) z_i, the normals of tag PCN.
-template <int PMAX, bool FULL>
-__device__ __forceinline__ void pcn_cells(uint64_t seed, uint32_t c0, uint32_t c1, uint32_t c3,
-                                          const Chunk& ch, double rho, double srho, double sdt,
-                                          const double* cur, double (&w)[PMAX]) {
-  double z[PMAX];
-  cell_normals<PMAX, FULL>(seed, c0, c1, SCH_TAG_PCN << 24, c3, ch, z);
-#pragma unroll
-  for (int j = 0; j < PMAX; ++j)
-    w[j] = slot_live<PMAX, FULL>(j, ch.cnt) ? rho * cur[j] + srho * (sdt * z[j]) : 0.0;
-}
-
 // n_jitter pCN moves of one particle's increments (section 3.1.2): proposal,
 // window rerun from the window-start state (re-read from global memory for
 // every proposal), likelihood and Metropolis accept in one launch.  With
@@ -694,8 +730,8 @@ __device__ __forceinline__ void pcn_cells(uint64_t seed, uint32_t c0, uint32_t c
 // proposal plus the fixed control and the potential is the likelihood plus
 // the Girsanov term sum (dLam^2 / 2 + dLam dW') / dt of the proposal.
 // MATERN: the increments are the DG0 cell values of the Matern-type noise;
-// each thread proposes its own cells step by step inside the window and
-// writes them to the stage row, and an acceptance swaps the roles of the
+// the threads propose pairs of cells step by step inside the window and
+// write them to the stage row, and an acceptance swaps the roles of the
 // particle's stage and increment rows (one copy back at the end if needed);
 // the per-cell controls are read only in the MCTRL variant, so that the
 // variant without them keeps its registers.
@@ -746,18 +782,29 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) k_
     if constexpr (MATERN) {
       const double sdt = sqrt(A.P.dt);
       const uint32_t step0 = A.cycle * static_cast<uint32_t>(S);
+      // cells 2 k and 2 k + 1 take the two normals of the PCN-tagged block
+      // (p, step, k | tag << 24, temper_k << 16 | move)
+      auto pair = [&](int n, int i, bool both) {
+        const size_t off = static_cast<size_t>(n) * nx + i;
+        pair_t c;
+        if (both) c = *reinterpret_cast<const pair8_t*>(cur + off);
+        else c = pair_t{cur[off], 0.0};
+        double za, zb;
+        normal2(A.seed, static_cast<uint32_t>(p), step0 + static_cast<uint32_t>(n),
+                static_cast<uint32_t>(i >> 1) | (SCH_TAG_PCN << 24), w3, za, zb);
+        pair_t w;
+        w.x = A.rho * c.x + srho * (sdt * za);
+        w.y = A.rho * c.y + srho * (sdt * zb);
+        if (both) *reinterpret_cast<pair8_t*>(prop + off) = w;
+        else prop[off] = w.x;
+        if (lam) {  // the window sees dW' + dLambda
+          w.x += lam[off];
+          if (both) w.y += lam[off + 1];
+        }
+        return w;
+      };
       auto noise = [&](int n, double (&e)[PMAX]) {
-        const size_t off = static_cast<size_t>(n) * nx + ch.start;
-        double w[PMAX];
-        pcn_cells<PMAX, FULL>(A.seed, static_cast<uint32_t>(p), step0 + static_cast<uint32_t>(n),
-                              w3, ch, A.rho, srho, sdt, cur + off, w);
-#pragma unroll
-        for (int jj = 0; jj < PMAX; ++jj)
-          if (slot_live<PMAX, FULL>(jj, ch.cnt)) {
-            prop[off + jj] = w[jj];
-            if (lam) w[jj] += lam[off + jj];  // the window sees dW' + dLambda
-          }
-        matern_add<PMAX, NT, FULL>(A.M, w, e, ch, L, t, par);
+        matern_noise<PMAX, NT, FULL, false>(A.M, pair, n, e, ch, X.row0(), L, t, nx, par);
       };
       st = run_window<PMAX, NT, FULL, false>(A.P, K, noise, S, m, u, ch, L, X, t, par, iters);
     } else {
@@ -775,11 +822,12 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) k_
     if (lam) {
       const double idt = 1.0 / A.P.dt;
       if constexpr (MATERN) {
-        // over the thread's own cells, which it wrote to the stage row itself
+        // over the cells that the thread wrote to the stage row itself
         for (int n = 0; n < S; ++n) {
-          const size_t off = static_cast<size_t>(n) * nx + ch.start;
-          for (int jj = 0; jj < ch.cnt; ++jj)
-            girs += (0.5 * lam[off + jj] * lam[off + jj] + lam[off + jj] * prop[off + jj]) * idt;
+          const size_t row = static_cast<size_t>(n) * nx;
+          for (int i = 2 * t; i < nx; i += 2 * NT)
+            for (size_t o = row + i; o < row + min(i + 2, nx); ++o)
+              girs += (0.5 * lam[o] * lam[o] + lam[o] * prop[o]) * idt;
         }
       } else {
         for (int i = t; i < S * Q; i += NT)
