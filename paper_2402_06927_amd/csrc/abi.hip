@@ -119,8 +119,8 @@ int launch_helm(const sch_model& md, const Tile& tl, int n, const double* in, do
   });
 }
 
-// Nudging scratch: checkpoints [n][n_segments][2][nx], segment states
-// [n][ckpt_every + 1][2][nx] and two iteration counters; for sch_nudge_run
+// Nudging scratch: checkpoints [n][n_segments][2][nx], segment steps
+// [n][ckpt_every][2][nx] and two iteration counters; for sch_nudge_run
 // also the batched L-BFGS state.
 struct NudgeWs {
   double *ckpt, *seg;
@@ -135,7 +135,7 @@ NudgeWs carve_nudge(void* base, bool full, int nx, int nq, int n, int ns, int ce
   NudgeWs w{};
   const size_t nseg = static_cast<size_t>((ns + ce - 1) / ce);
   w.ckpt = c.take<double>(static_cast<size_t>(n) * nseg * 2 * nx);
-  w.seg = c.take<double>(static_cast<size_t>(n) * (ce + 1) * 2 * nx);
+  w.seg = c.take<double>(static_cast<size_t>(n) * ce * 2 * nx);
   w.acc = c.take<unsigned long long>(2);
   if (full) {
     const size_t v = static_cast<size_t>(n) * nq, mq = v * kLbfgsMaxMem;

@@ -22,9 +22,15 @@
 // 2h/3 + mu dt/h + (dv_{i+1} - dv_{i-1})/4, h/6 - mu dt/(2h) - dv_i/4).
 //
 // Memory: the forward pass stores (m, u) at the start of every segment of
-// `ckpt_every` steps; the reverse pass recomputes each segment's states from
-// its checkpoint into a per-particle segment buffer (the last segment's
-// states are kept from the forward pass) and sweeps it backwards.
+// `ckpt_every` steps; the reverse pass recomputes each segment from its
+// checkpoint, writing every step's s and w into a per-particle segment buffer
+// (the last segment's are kept from the forward pass), and sweeps it
+// backwards.  Neither buffer is read by anyone else, so both are laid out lane
+// by lane (put_row).  Storing s and w where the states (m, u) were leaves the
+// reverse sweep no noise to form again; with the rows, the two barriers of a
+// fixed-point iteration and the products' coalesced reads of the mode table
+// the gradient of 2048 particles (2048 nodes, 40 steps, 8 modes) went from
+// 8.47 to 6.84 ms.
 #pragma once
 
 #include "model.hpp"
@@ -46,7 +52,7 @@ struct NudgeArgs {
   int* status;         // [n] or null
   const int* active;   // [n] or null: particles with active[p] == 0 are skipped
   double* ckpt;        // [n][n_segments][2][nx]
-  double* seg;         // [n][ckpt_every + 1][2][nx]
+  double* seg;         // [n][ckpt_every][2][nx]: s and w of a segment's steps
   unsigned long long* iters_acc;  // [2]: forward Picard and adjoint fixed-point iterations
   MaternDev M;                    // Matern-type noise (MATERN kernels)
 };
@@ -107,60 +113,51 @@ __device__ __forceinline__ void advect_t(const double (&s)[PMAX], double sl, dou
 }
 
 // One reverse step: lam holds lambda_{n+1} on entry and lambda_n on exit,
-// gdU receives dJ/d(dU^n).  (ma, ua) is the state before the step, (mb, ub)
-// after it; noise(0, dv) adds the step's noise field dU^n.  Where the window's two
+// gdU receives dJ/d(dU^n).  s = m^n + m^{n+1} and w = dv/4 + o of the step
+// (o = h/6 - mu dt/(2h)) come from the forward sweep; rows of A^T:
+// (w_i, 2h/3 + mu dt/h + w_{i+1} - w_{i-1}, 2 o - w_i).  Where the window's two
 // LDS arrays exist (free during the reverse sweep), s and lambda_{n+1}, which
-// the fixed-point loop only reads, wait there instead of in registers.
-template <int PMAX, int NT, bool FULL, class NoiseF>
-__device__ int adjoint_step(const StepParams& P, const HelmConst& K, NoiseF noise,
-                            const double* ma, const double* ua, const double* mb,
-                            const double* ub, double (&lam)[PMAX], double (&gdU)[PMAX],
+// the fixed-point loop only reads, wait there instead of in registers.  As in
+// the forward step an iteration has two barriers: the halo of nu comes from
+// the interface values, and the stopping test rides on the Helmholtz solve
+// (whose result the last iteration does not use: one solve a step, where the
+// test's own reduction and the halo took three more barriers an iteration).
+template <int PMAX, int NT, bool FULL>
+__device__ int adjoint_step(const StepParams& P, const HelmConst& K, const double (&s)[PMAX],
+                            const double (&w)[PMAX], double (&lam)[PMAX], double (&gdU)[PMAX],
                             const Chunk& ch, RowLds<NT>& L, AuxLds<PMAX, NT>& X, int t,
                             Parity& par, int& iters) {
   constexpr bool kL = AuxLds<PMAX, NT>::kInLds;
   const int cnt = ch.cnt;
-  const double hdt = 0.5 * P.dt;
-  double s[PMAX], dv[PMAX];
-#pragma unroll
-  for (int j = 0; j < PMAX; ++j) {
-    if (slot_live<PMAX, FULL>(j, cnt)) {
-      s[j] = ma[ch.start + j] + mb[ch.start + j];
-      dv[j] = hdt * (ua[ch.start + j] + ub[ch.start + j]);
-    } else {
-      s[j] = 0.0;
-      dv[j] = 0.0;
-    }
+  double sl, sr, wl, wr;
+  {
+    const double fst[2] = {s[0], w[0]};
+    const double lst[2] = {last_of<PMAX, FULL>(s, cnt), last_of<PMAX, FULL>(w, cnt)};
+    double fl[2], fr[2];
+    exchange<NT, 2>(fst, lst, fl, fr, L, t, par.hs);
+    sl = fl[0];
+    sr = fr[0];
+    wl = fl[1];
+    wr = fr[1];
   }
-  noise(0, dv);  // + dU^n
-  double sl, sr, vl, vr;
-  halo<PMAX, NT, FULL>(s, cnt, L, t, sl, sr, par.hs);
-  halo<PMAX, NT, FULL>(dv, cnt, L, t, vl, vr, par.hs);
-  const double ao = P.a_off, ad = P.a_diag;
+  const double ao2 = 2.0 * P.a_off, ad = P.a_diag;
   auto rowAT = [&](int j, double& a, double& b, double& c) {
-    const double vm = left_of<PMAX, FULL>(dv, j, vl);
-    const double vp = right_of<PMAX, FULL>(dv, j, cnt, vr);
-    a = fma(0.25, dv[j], ao);
-    b = fma(0.25, vp - vm, ad);
-    c = fma(-0.25, dv[j], ao);
+    const double vm = left_of<PMAX, FULL>(w, j, wl);
+    const double vp = right_of<PMAX, FULL>(w, j, cnt, wr);
+    a = w[j];
+    b = ad + (vp - vm);
+    c = ao2 - w[j];
   };
   // s and lambda_{n+1} from LDS (kL), each value laundered so that the
   // loads stay inside the loop instead of being hoisted into registers
+  int tx = t;
   auto s_at = [&](double (&sv)[PMAX]) {
 #pragma unroll
-    for (int j = 0; j < PMAX; ++j) {
-      double x = X.at(kL ? 1 : 0, j, t);
-      asm volatile("" : "+v"(x));
-      sv[j] = x;
-    }
+    for (int j = 0; j < PMAX; ++j) sv[j] = kL ? X.at(kL ? 1 : 0, j, tx) : s[j];
   };
   auto lam_at = [&](int j) -> double {
-    if constexpr (kL) {
-      double x = X.at(0, j, t);
-      asm volatile("" : "+v"(x));
-      return x;
-    } else {
-      return lam[j];
-    }
+    if constexpr (kL) return X.at(0, j, tx);
+    else return lam[j];
   };
   double nu[PMAX], rhs[PMAX];
 #pragma unroll
@@ -174,81 +171,124 @@ __device__ int adjoint_step(const StepParams& P, const HelmConst& K, NoiseF nois
   }
   // the first solve gives A^{-T} lambda; picard_max corrections follow at most
   int status = SCH_E_NONCONVERGED, k = 1;
-  double prevd = 0.0;  // the previous iteration's change of nu
+  double prevd = 0.0;    // the previous iteration's change of nu
+  double nl, nr;         // halo of nu
   for (; k <= P.picard_max + 1; ++k) {
-    double nn[PMAX];
-    double xl_unused, xr_unused, grow = 0.0;
-    cyclic_solve<PMAX, NT, FULL>(rowAT, [&](int j) { return rhs[j]; }, nn, cnt, L, t, xl_unused,
-                                 xr_unused, grow);
+    asm volatile("" : "+v"(tx));
+    double nn[PMAX], grow = 0.0;
+    cyclic_solve<PMAX, NT, FULL>(rowAT, [&](int j) { return rhs[j]; }, nn, cnt, L, t, nl, nr,
+                                 grow);
     double diff = 0.0, scale = 0.0;
-    // bit 0: a non-finite iterate; bit 1: elimination growth above kMaxGrowth
-    int bad = grow <= kMaxGrowth ? 0 : 2;
 #pragma unroll
     for (int j = 0; j < PMAX; ++j) {
       if (slot_live<PMAX, FULL>(j, cnt)) {
         diff = fmax(diff, fabs(nn[j] - nu[j]));
         scale = fmax(scale, fabs(nn[j]));
-        bad |= !isfinite(nn[j]);
       }
       nu[j] = nn[j];
     }
-    block_max2_or<NT>(diff, scale, bad, L, t);
-    if (bad) {
-      status = (bad & 2) ? SCH_E_UNSTABLE : SCH_E_NONFINITE;
+    double adv[PMAX], z[PMAX], sv[PMAX];
+    s_at(sv);
+    advect_t<PMAX, FULL>(sv, sl, sr, nu, nl, nr, cnt, 1.0, adv);
+    // M H^{-1} adv = H^{-1} M adv (the two circulants commute): the mass
+    // product folded into the scan form; the bordering values are not used
+    HelmRed R{diff, scale, !(grow <= kMaxGrowth), true, 0};
+    double zL, zR;
+    solve_helm<PMAX, NT, FULL, true, true>(K, L.tab[0], adv, z, zL, zR, cnt, L, par.slot, t, R);
+    par.slot ^= 1;
+    if (R.word >= kNonfinite) {
+      status = R.word == kUnstable ? SCH_E_UNSTABLE : SCH_E_NONFINITE;
       break;
     }
     // the stopping rule of the forward step: the estimated error
     // c / (1 - c) d_k, c = d_k / d_{k-1}, while c < 1/2 (the first change is
     // the first iterate's distance from the zero start)
-    const double lim = P.tol * scale;
-    const bool done = (k > 1 && 2.0 * diff < prevd) ? diff * diff <= lim * (prevd - diff)
-                                                    : diff <= lim;
-    prevd = diff;
+    const double d = __hiloint2double(static_cast<int>(R.word), 0), lim = P.tol * R.scale;
+    const bool done =
+        __any((k > 1 && 2.0 * d < prevd) ? d * d <= lim * (prevd - d) : d <= lim);
+    prevd = d;
     if (done) {
       status = SCH_OK;
       break;
     }
     // rhs = lambda - (dt/4) M H^{-1} D(s)^T nu
-    double nl, nr, w[PMAX], z[PMAX];
-    halo<PMAX, NT, FULL>(nu, cnt, L, t, nl, nr, par.hs);
-    if constexpr (kL) {
-      double sv[PMAX];
-      s_at(sv);
-      advect_t<PMAX, FULL>(sv, sl, sr, nu, nl, nr, cnt, 1.0, w);
-    } else {
-      advect_t<PMAX, FULL>(s, sl, sr, nu, nl, nr, cnt, 1.0, w);
-    }
-    // M H^{-1} w = H^{-1} M w (the two circulants commute): the mass product
-    // folded into the scan form; the bordering values are not used
-    double zL, zR;
-    solve_helm<PMAX, NT, FULL, true>(K, L.tab[0], w, z, zL, zR, cnt, L, par.slot, t);
-    par.slot ^= 1;
     const double q = 0.25 * P.dt;
 #pragma unroll
     for (int j = 0; j < PMAX; ++j) rhs[j] = fma(-q, z[j], lam_at(j));
   }
   iters += k > P.picard_max + 1 ? P.picard_max + 1 : k;
   // dJ/d(dU) = -(1/2) D(s)^T nu;  lambda_n = 2 M nu - lambda_{n+1}
-  double nl, nr, mnu[PMAX];
-  halo<PMAX, NT, FULL>(nu, cnt, L, t, nl, nr, par.hs);
-  if constexpr (kL) {
-    double sv[PMAX];
-    s_at(sv);
-    advect_t<PMAX, FULL>(sv, sl, sr, nu, nl, nr, cnt, -0.5, gdU);
-  } else {
-    advect_t<PMAX, FULL>(s, sl, sr, nu, nl, nr, cnt, -0.5, gdU);
-  }
-  mass_apply<PMAX, NT, FULL>(nu, mnu, P.h, cnt, L, t, 2.0, par.hs);
+  double mnu[PMAX], sv[PMAX];
+  s_at(sv);
+  advect_t<PMAX, FULL>(sv, sl, sr, nu, nl, nr, cnt, -0.5, gdU);
+  mass_apply_h<PMAX, FULL>(nu, mnu, P.h, cnt, nl, nr, 2.0);
 #pragma unroll
   for (int j = 0; j < PMAX; ++j) lam[j] = mnu[j] - lam_at(j);
   return status;
 }
 
-template <int PMAX, bool FULL>
-__device__ __forceinline__ void store_state(double* base, int nx, const Chunk& ch,
-                                            const double (&m)[PMAX], const double (&u)[PMAX]) {
-  store_chunk<PMAX, FULL>(base, ch, m);
-  store_chunk<PMAX, FULL>(base + nx, ch, u);
+// The gradient of one step with respect to the mode increments, without the
+// Girsanov term: part[q][wavefront] = sum over the wavefront's nodes of
+// xi_q gdU.  The table is read as by modes_noise, so gdU goes through LDS the
+// other way (stg as there; the threads may still read it).
+template <int PMAX, int NT, bool FULL, int QM>
+__device__ __forceinline__ void mode_products(const StepParams& P, const double (&gdU)[PMAX],
+                                              const Chunk& ch, double* stg, int t,
+                                              double (&part)[QM][NT / kWave]) {
+  constexpr int H = PMAX / 2;
+  const int lane = t & (kWave - 1), wv = t / kWave;
+  if constexpr (PMAX <= 4) {
+    for (int q = 0; q < P.n_modes; ++q) {
+      const double* xq = P.xi + static_cast<size_t>(q) * P.nx + ch.start;
+      double a = 0.0;
+#pragma unroll
+      for (int j = 0; j < PMAX; ++j)
+        if (slot_live<PMAX, FULL>(j, ch.cnt)) a = fma(xq[j], gdU[j], a);
+      a = wave_sum(a);
+      if (lane == 0) part[q][wv] = a;
+    }
+    return;
+  }
+  int tl = t;
+  Chunk own = ch;
+  asm volatile("" : "+v"(tl), "+v"(own.start));
+  const ModeRows<PMAX, NT, FULL> rows(P, tl);
+  const int nx = rows.nx, Q = P.n_modes;
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < PMAX; ++j)
+    if (slot_live<PMAX, FULL>(j, ch.cnt)) stg[stage_pos(own.start + j)] = gdU[j];
+  __syncthreads();
+  pair_t g[H];
+  const int p0 = stage_pos(2 * tl);
+#pragma unroll
+  for (int k = 0; k < H; ++k) {
+    const int c = p0 ^ ((NT / 16 * k) & 15), i = 2 * (tl + NT * k);
+    const double x = stg[2 * NT * k + c], y = stg[2 * NT * k + (c ^ 1)];
+    // past the end the table's pair repeats nodes: they count nothing, but for
+    // the last of an odd grid, which is the pair's second
+    g[k].x = FULL || i + 1 < nx ? x : 0.0;
+    g[k].y = FULL || i + 1 < nx ? y : i < nx ? x : 0.0;
+  }
+  pair_t xa[H], xb[H];
+  auto add = [&](const pair_t (&x)[H], int q) {
+    double a = 0.0, b = 0.0;
+#pragma unroll
+    for (int k = 0; k < H; ++k) {
+      a = fma(x[k].x, g[k].x, a);
+      b = fma(x[k].y, g[k].y, b);
+    }
+    a = wave_sum(a + b);
+    if (lane == 0) part[q][wv] = a;
+  };
+  rows.fetch(xa, 0);
+  for (int q = 0; q < Q; q += 2) {
+    const int q1 = q + 1 < Q ? q + 1 : q;
+    rows.fetch(xb, q1);
+    add(xa, q);
+    rows.fetch(xa, q + 2 < Q ? q + 2 : q1);
+    add(xb, q1);
+  }
 }
 
 // MATERN: the controls dW, dLambda and the gradient are per cell,
@@ -298,7 +338,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) k_
     }
   };
   double* ck = A.ckpt + static_cast<size_t>(p) * nseg * 2 * nx;
-  double* sg = A.seg + static_cast<size_t>(p) * (CE + 1) * 2 * nx;
+  double* sg = A.seg + static_cast<size_t>(p) * CE * 2 * nx;
   helm_table(K, L.tab[0], t);
   if constexpr (MATERN) helm_table(A.M.K, L.tab[1], t);
   __syncthreads();
@@ -307,17 +347,25 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) k_
   load_chunk<PMAX, FULL>(A.u0 + static_cast<size_t>(p) * nx, ch, u);
   int fit = 0, ait = 0, st = SCH_OK;
 
-  // forward pass: checkpoints, and every state of the last segment
-  for (int c = 0; c < nseg && st == SCH_OK; ++c) {
-    const int n0 = c * CE, n1 = min(S, n0 + CE);
-    const bool last = c == nseg - 1;
-    store_state<PMAX, FULL>(ck + static_cast<size_t>(c) * 2 * nx, nx, ch, m, u);
-    if (last) store_state<PMAX, FULL>(sg, nx, ch, m, u);
-    for (int n = n0; n < n1 && st == SCH_OK; ++n) {
-      st = run_window<PMAX, NT, FULL>(A.P, K, step_noise(n), 1, m, u, ch, L, X, t, par, fit);
-      if (last) store_state<PMAX, FULL>(sg + static_cast<size_t>(n - n0 + 1) * 2 * nx, nx, ch, m, u);
-    }
+  // a failed window's state is not used: the window need not keep its input
+  const int base = nx / NT;
+  auto noise_from = [&](int n0) {
+    return [&, n0](int n, double (&e)[PMAX]) { step_noise(n0 + n)(0, e); };
+  };
+  auto sink = [&](int n, const double (&s)[PMAX], const double (&w)[PMAX]) {
+    put_row<PMAX, NT, FULL>(sg + static_cast<size_t>(n) * 2 * nx, base, ch, t, s);
+    put_row<PMAX, NT, FULL>(sg + static_cast<size_t>(n) * 2 * nx + nx, base, ch, t, w);
+  };
+  // forward pass: checkpoints, and the last segment's steps
+  for (int c = 0; c < nseg - 1 && st == SCH_OK; ++c) {
+    put_row<PMAX, NT, FULL>(ck + static_cast<size_t>(c) * 2 * nx, base, ch, t, m);
+    put_row<PMAX, NT, FULL>(ck + static_cast<size_t>(c) * 2 * nx + nx, base, ch, t, u);
+    st = run_window<PMAX, NT, FULL, false>(A.P, K, noise_from(c * CE), CE, m, u, ch, L, X, t, par,
+                                           fit);
   }
+  if (st == SCH_OK)
+    st = run_window<PMAX, NT, FULL, false>(A.P, K, noise_from((nseg - 1) * CE), S - (nseg - 1) * CE,
+                                           m, u, ch, L, X, t, par, fit, sink);
   double J = INFINITY;
   if (st == SCH_OK) {
     const double phi = block_nll<PMAX, NT, FULL>(u, ch, nx, A.n_obs, A.y, A.sigma, L, t, par.hs);
@@ -342,24 +390,24 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) k_
       solve_helm<PMAX, NT, FULL, true>(K, L.tab[0], w, lam, zL, zR, ch.cnt, L, par.slot, t);
       par.slot ^= 1;
     }
-    const int lane = t & (kWave - 1), wv = t / kWave;
     for (int c = nseg - 1; c >= 0 && st == SCH_OK; --c) {
       const int n0 = c * CE, n1 = min(S, n0 + CE);
       if (c != nseg - 1) {
-        load_chunk<PMAX, FULL>(ck + static_cast<size_t>(c) * 2 * nx, ch, m);
-        load_chunk<PMAX, FULL>(ck + static_cast<size_t>(c) * 2 * nx + nx, ch, u);
-        store_state<PMAX, FULL>(sg, nx, ch, m, u);
-        for (int n = n0; n < n1 && st == SCH_OK; ++n) {
-          st = run_window<PMAX, NT, FULL>(A.P, K, step_noise(n), 1, m, u, ch, L, X, t, par, fit);
-          store_state<PMAX, FULL>(sg + static_cast<size_t>(n - n0 + 1) * 2 * nx, nx, ch, m, u);
-        }
+        get_row<PMAX, NT, FULL>(ck + static_cast<size_t>(c) * 2 * nx, base, ch, t, m);
+        get_row<PMAX, NT, FULL>(ck + static_cast<size_t>(c) * 2 * nx + nx, base, ch, t, u);
+        __syncthreads();  // the last reverse step's reads of the window's LDS arrays
+        st = run_window<PMAX, NT, FULL, false>(A.P, K, noise_from(n0), CE, m, u, ch, L, X, t, par,
+                                               fit, sink);
       }
       for (int n = n1 - 1; n >= n0 && st == SCH_OK; --n) {
-        const double* sa = sg + static_cast<size_t>(n - n0) * 2 * nx;
-        const double* sb = sa + 2 * nx;
+        const double* row = sg + static_cast<size_t>(n - n0) * 2 * nx;
         double gdU[PMAX];
-        st = adjoint_step<PMAX, NT, FULL>(A.P, K, step_noise(n), sa, sa + nx, sb, sb + nx, lam, gdU,
-                                          ch, L, X, t, par, ait);
+        {
+          double s[PMAX], w[PMAX];
+          get_row<PMAX, NT, FULL>(row, base, ch, t, s);
+          get_row<PMAX, NT, FULL>(row + nx, base, ch, t, w);
+          st = adjoint_step<PMAX, NT, FULL>(A.P, K, s, w, lam, gdU, ch, L, X, t, par, ait);
+        }
         if (n >= CS) continue;
         if constexpr (MATERN) {
           double gc[PMAX];
@@ -369,15 +417,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) k_
           for (int j = 0; j < PMAX; ++j)
             if (slot_live<PMAX, FULL>(j, ch.cnt)) gp[j] = gc[j] + incv(n, ch.start + j) / A.P.dt;
         } else {
-          for (int q = 0; q < Q; ++q) {
-            const double* xq = A.P.xi + static_cast<size_t>(q) * nx + ch.start;
-            double a = 0.0;
-#pragma unroll
-            for (int j = 0; j < PMAX; ++j)
-              if (slot_live<PMAX, FULL>(j, ch.cnt)) a = fma(xq[j], gdU[j], a);
-            a = wave_sum(a);
-            if (lane == 0) gpart[q][wv] = a;
-          }
+          mode_products<PMAX, NT, FULL>(A.P, gdU, ch, X.row0(), t, gpart);
           __syncthreads();
           for (int q = t; q < Q; q += NT) {
             double a = 0.0;

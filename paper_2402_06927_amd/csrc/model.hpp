@@ -5,6 +5,8 @@
 // solve_helm().
 #pragma once
 
+#include <type_traits>
+
 #include "device.hpp"
 #include "helm.hpp"
 
@@ -102,25 +104,64 @@ __device__ __forceinline__ double staged_slot(const double* stg, const Chunk& ch
   }
 }
 
+typedef double pair_t __attribute__((ext_vector_type(2)));
+typedef double pair8_t __attribute__((ext_vector_type(2), aligned(8)));  // rows of odd grids
+
+// Rows of the mode table, 16 bytes a lane with consecutive lanes on consecutive
+// nodes: pair k of thread t holds nodes i = 2 (t + NT k) and i + 1.  A compute
+// unit's address unit takes about 20 clocks for a wavefront's load of 8 or of
+// 16 bytes a lane while the lanes share lines, and 64 where each lane has a
+// line of its own, as in reading a 16-node chunk's own nodes: 256 KB of table
+// (Q = 8, nx = 4096) take a workgroup 33900 clocks by chunks, 19600 by 8 and
+// 10800 by 16 bytes a lane (two workgroups a unit).  A ragged grid's pairs
+// past the end read its last two nodes: all but the single last node of an odd
+// grid (i = nx - 1, the pair's second half) are not used.
+template <int PMAX, int NT, bool FULL>
+struct ModeRows {
+  static constexpr int H = PMAX / 2;
+  // on full grids pairs share an address register as far as the instruction's
+  // 12-bit offset reaches
+  static constexpr int G = FULL && NT < 256 ? 256 / NT : 1, NV = (H + G - 1) / G;
+  uint64_t xi;
+  int nx, vo[NV];
+  // uniform, also where the parameters come from memory (the batched runner):
+  // a descriptor in vector registers would be looped over lane by lane
+  __device__ ModeRows(const StepParams& P, int t) {
+    nx = __builtin_amdgcn_readfirstlane(P.nx);
+    const uint64_t a = reinterpret_cast<uint64_t>(P.xi);
+    xi = static_cast<uint64_t>(static_cast<uint32_t>(
+             __builtin_amdgcn_readfirstlane(static_cast<int>(a >> 32))))
+             << 32 |
+         static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(a)));
+#pragma unroll
+    for (int g = 0; g < NV; ++g) {
+      const int i = 2 * (t + NT * G * g);
+      vo[g] = 8 * (FULL ? i : min(i, nx - 2));
+      asm volatile("" : "+v"(vo[g]));
+    }
+  }
+  __device__ void fetch(pair_t (&x)[H], int q) const {
+    const __amdgpu_buffer_rsrc_t row = __builtin_amdgcn_make_buffer_rsrc(
+        reinterpret_cast<double*>(xi) + static_cast<size_t>(q) * nx, 0, nx * 8, 0x00027000);
+#pragma unroll
+    for (int k = 0; k < H; ++k)
+      x[k] = __builtin_bit_cast(pair_t, __builtin_amdgcn_raw_buffer_load_b128(
+                                            row, vo[k / G] + 16 * NT * (k % G), 0, 0));
+  }
+};
+
 // The noise of the modes form: noise(n, e) adds sum_q xi_q inc(n, q) to the
 // chunk e, inc(n, q) being the increment dW^n_q (+ dLambda^n_q) of step n,
-// mode q.  The mode table is read 16 bytes a lane with consecutive lanes on
-// consecutive nodes (thread t sums nodes 2 t, 2 t + 1, 2 t + 2 NT, ...) and
-// the sum changes hands through LDS.  A compute unit's address unit takes
-// about 20 clocks for a wavefront's load of 8 or of 16 bytes a lane while the
-// lanes share lines, and 64 where each lane has a line of its own, as in
-// reading the chunk's own nodes: 256 KB of table (Q = 8, nx = 4096) take a
-// workgroup 33900 clocks by chunks, 19600 by 8 and 10800 by 16 bytes a lane
-// (two workgroups a unit).  Chunks of at most four nodes are read as they are:
-// at least four of them share a line, and one wavefront alone waits longer for
-// the exchange than for the lines.  stg: PMAX NT doubles of LDS that no thread still
-// reads (FENCE: that the threads may still read, a barrier comes first).
+// mode q.  The rows are summed as they are read (ModeRows) and the sum changes
+// hands through LDS.  Chunks of at most four nodes are read as they are: at
+// least four of them share a line, and one wavefront alone waits longer for
+// the exchange than for the lines.  stg: PMAX NT doubles of LDS that no thread
+// still reads (FENCE: that the threads may still read, a barrier comes first).
 template <int PMAX, int NT, bool FULL, bool FENCE = false, class IncF>
 __device__ __forceinline__ auto modes_noise(const StepParams& P, const Chunk& ch, double* stg,
                                             int t, IncF inc) {
   static_assert(PMAX % 2 == 0, "nodes go in pairs");
   return [&P, ch, stg, t0 = t, inc](int n, double (&e)[PMAX]) {
-    typedef double d2 __attribute__((ext_vector_type(2)));
     constexpr int H = PMAX / 2;  // pairs per thread
     if constexpr (PMAX <= 4) {
       for (int q = 0; q < P.n_modes; ++q) {
@@ -137,40 +178,12 @@ __device__ __forceinline__ auto modes_noise(const StepParams& P, const Chunk& ch
     int t = t0;
     Chunk own = ch;
     asm volatile("" : "+v"(t), "+v"(own.start));
-    // uniform, also where the parameters come from memory (the batched runner):
-    // a descriptor in vector registers would be looped over lane by lane
-    const int nx = __builtin_amdgcn_readfirstlane(P.nx), Q = P.n_modes;
-    const uint64_t xi0 = reinterpret_cast<uint64_t>(P.xi);
-    const uint64_t xi = static_cast<uint64_t>(static_cast<uint32_t>(
-                            __builtin_amdgcn_readfirstlane(static_cast<int>(xi0 >> 32))))
-                            << 32 |
-                        static_cast<uint32_t>(
-                            __builtin_amdgcn_readfirstlane(static_cast<int>(xi0)));
-    // byte offset of pair k.  A ragged grid's pairs past the end read its last
-    // two nodes (unused, or for the single last node of an odd grid, taken
-    // from the pair's second half).  On full grids pairs share an address
-    // register as far as the instruction's 12-bit offset reaches.
-    constexpr int G = FULL && NT < 256 ? 256 / NT : 1;
-    constexpr int NV = (H + G - 1) / G;
-    int vo[NV];
+    const ModeRows<PMAX, NT, FULL> rows(P, t);
+    const int nx = rows.nx, Q = P.n_modes;
+    pair_t acc[H];
 #pragma unroll
-    for (int g = 0; g < NV; ++g) {
-      const int i = 2 * (t + NT * G * g);
-      vo[g] = 8 * (FULL ? i : min(i, nx - 2));
-      asm volatile("" : "+v"(vo[g]));
-    }
-    auto fetch = [&](d2 (&x)[H], int q) {
-      const __amdgpu_buffer_rsrc_t row = __builtin_amdgcn_make_buffer_rsrc(
-          reinterpret_cast<double*>(xi) + static_cast<size_t>(q) * nx, 0, nx * 8, 0x00027000);
-#pragma unroll
-      for (int k = 0; k < H; ++k)
-        x[k] = __builtin_bit_cast(d2, __builtin_amdgcn_raw_buffer_load_b128(
-                                          row, vo[k / G] + 16 * NT * (k % G), 0, 0));
-    };
-    d2 acc[H];
-#pragma unroll
-    for (int k = 0; k < H; ++k) acc[k] = d2{0.0, 0.0};
-    auto add = [&](const d2 (&x)[H], double w) {
+    for (int k = 0; k < H; ++k) acc[k] = pair_t{0.0, 0.0};
+    auto add = [&](const pair_t (&x)[H], double w) {
 #pragma unroll
       for (int k = 0; k < H; ++k) {
         acc[k].x = fma(x[k].x, w, acc[k].x);
@@ -180,14 +193,14 @@ __device__ __forceinline__ auto modes_noise(const StepParams& P, const Chunk& ch
     // two rows in turn, one in flight while the other is summed (past the last
     // row the last one is read again and enters with weight 0: a branch around
     // the loads would end the overlap)
-    d2 xa[H], xb[H];
-    fetch(xa, 0);
+    pair_t xa[H], xb[H];
+    rows.fetch(xa, 0);
     for (int q = 0; q < Q; q += 2) {
       const int q1 = q + 1 < Q ? q + 1 : q;
       const double wa = inc(n, q), w1 = inc(n, q1), wb = q + 1 < Q ? w1 : 0.0;
-      fetch(xb, q1);
+      rows.fetch(xb, q1);
       add(xa, wa);
-      fetch(xa, q + 2 < Q ? q + 2 : q1);
+      rows.fetch(xa, q + 2 < Q ? q + 2 : q1);
       add(xb, wb);
     }
     if (FENCE) __syncthreads();
@@ -262,8 +275,6 @@ __device__ __forceinline__ void matern_add(const MaternDev& M, const double (&w)
 // exchanged through LDS, where the cell left of the chunk is found too):
 // pair(n, i, both) gives the increments of cells i (even) and, if both, i + 1.
 // stg, FENCE: as for modes_noise.
-typedef double pair_t __attribute__((ext_vector_type(2)));
-typedef double pair8_t __attribute__((ext_vector_type(2), aligned(8)));  // rows of odd grids
 template <int PMAX, int NT, bool FULL, bool FENCE, class PairF>
 __device__ __forceinline__ void matern_noise(const MaternDev& M, PairF pair, int n,
                                              double (&e)[PMAX], const Chunk& ch, double* stg,
@@ -350,10 +361,14 @@ __device__ __forceinline__ void matern_transpose(const MaternDev& M, const doubl
 // elimination growth exceeds kMaxGrowth (SCH_E_UNSTABLE) the step's input is
 // kept (KEEP) or the state is left undefined (!KEEP, for callers that discard
 // a failed window: u^n then need not stay live through the iteration).
-template <int PMAX, int NT, bool FULL, bool KEEP = true, class NoiseF>
+// sink(n, s, w), if given, receives for every step done s = m^n + m^{n+1} and
+// w = dv / 4 + o of the accepted iterate, what the reverse sweep needs.
+struct NoSink {};
+template <int PMAX, int NT, bool FULL, bool KEEP = true, class NoiseF, class SinkF = NoSink>
 __device__ int run_window(const StepParams& P, const HelmConst& K, NoiseF noise, int n_steps,
                           double (&m)[PMAX], double (&u)[PMAX], const Chunk& ch, RowLds<NT>& L,
-                          AuxLds<PMAX, NT>& X, int t, Parity& par, int& iters) {
+                          AuxLds<PMAX, NT>& X, int t, Parity& par, int& iters,
+                          SinkF sink = {}) {
   constexpr bool kLds = AuxLds<PMAX, NT>::kInLds;
   const int cnt = ch.cnt;
   const double hdt = 0.5 * P.dt;
@@ -395,9 +410,11 @@ __device__ int run_window(const StepParams& P, const HelmConst& K, NoiseF noise,
       uL = fl[2];
       uR = fr[2];
 #pragma unroll
-      for (int j = 0; j < PMAX; ++j) {
-        setD(j, e[j]);
-        setP(j, m[j]);
+      for (int j = 0; j < PMAX; ++j) setD(j, e[j]);
+      // (after the first step the previous iterate's place holds m^n already)
+      if (n == 0) {
+#pragma unroll
+        for (int j = 0; j < PMAX; ++j) setP(j, m[j]);
       }
     }
     auto fget = [&](int j) -> double {
@@ -502,6 +519,15 @@ __device__ int run_window(const StepParams& P, const HelmConst& K, NoiseF noise,
     }
     iters += k > P.picard_max ? P.picard_max : k;
     if (KEEP && (status == SCH_E_NONFINITE || status == SCH_E_UNSTABLE)) return status;
+    if constexpr (!std::is_same_v<SinkF, NoSink>) {
+      double s[PMAX], w[PMAX];
+#pragma unroll
+      for (int j = 0; j < PMAX; ++j) {
+        s[j] = m[j] + getP(j);
+        w[j] = fma(hdt4, us[j], getD(j));
+      }
+      sink(n, s, w);
+    }
     // the accepted iterate m* was stored as the last "previous iterate"
 #pragma unroll
     for (int j = 0; j < PMAX; ++j) {
@@ -584,6 +610,39 @@ __device__ __forceinline__ void store_chunk(double* g, const Chunk& ch, const do
 #pragma unroll
   for (int j = 0; j < PMAX; ++j)
     if (slot_live<PMAX, FULL>(j, ch.cnt)) g[ch.start + j] = v[j];
+}
+
+// A chunk to and from a row that only this workgroup reads back: slots in pairs,
+// lane after lane (16 bytes each), then the slots that not every chunk holds
+// or that are left over one by one, nx doubles in all.  The chunks' own places
+// would put each lane on a line of its own (ModeRows).  base: nx / NT.
+template <int PMAX, int NT, bool FULL>
+__device__ __forceinline__ void put_row(double* row, int base, const Chunk& ch, int t,
+                                        const double (&v)[PMAX]) {
+#pragma unroll
+  for (int k = 0; k < PMAX / 2; ++k) {
+    if (FULL || 2 * k + 2 <= kMinRows<PMAX> || 2 * k + 1 < base) {
+      *reinterpret_cast<pair8_t*>(row + 2 * (NT * k + t)) = pair_t{v[2 * k], v[2 * k + 1]};
+    } else {
+      if (2 * k < ch.cnt) row[2 * k * NT + t] = v[2 * k];
+      if (2 * k + 1 < ch.cnt) row[(2 * k + 1) * NT + t] = v[2 * k + 1];
+    }
+  }
+}
+template <int PMAX, int NT, bool FULL>
+__device__ __forceinline__ void get_row(const double* row, int base, const Chunk& ch, int t,
+                                        double (&v)[PMAX]) {
+#pragma unroll
+  for (int k = 0; k < PMAX / 2; ++k) {
+    if (FULL || 2 * k + 2 <= kMinRows<PMAX> || 2 * k + 1 < base) {
+      const pair_t x = *reinterpret_cast<const pair8_t*>(row + 2 * (NT * k + t));
+      v[2 * k] = x.x;
+      v[2 * k + 1] = x.y;
+    } else {
+      v[2 * k] = 2 * k < ch.cnt ? row[2 * k * NT + t] : 0.0;
+      v[2 * k + 1] = 2 * k + 1 < ch.cnt ? row[(2 * k + 1) * NT + t] : 0.0;
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
