@@ -1,7 +1,7 @@
 """Tile autotuner of the model kernels.
 
 A particle's row of nx nodes is split over NT threads (a power of two,
-64..512) holding nx / NT nodes each (4, 8 or 16 register slots; 2 on one
+64..512) holding nx / NT nodes each (4, 6, 8, 12 or 16 register slots; 2 on one
 wavefront for nx <= 128).  For a grid
 size the tuner times the library's ensemble step (``sch_ensemble_step``, the
 kernel every filter stage reruns) on the caller's own ensemble for every
@@ -20,15 +20,14 @@ import torch
 from . import sch
 
 # (threads per particle, register slots) of the compiled model kernels
-TILES = ((64, 2), (64, 4), (64, 8), (64, 16), (128, 8), (128, 16), (256, 8), (256, 16), (512, 8),
-         (512, 16))
+TILES = ((64, 2), (64, 4)) + tuple((nt, p) for nt in (64, 128, 256, 512) for p in (6, 8, 12, 16))
 
 
 def slots(nx: int, nt: int) -> int:
     need = math.ceil(nx / nt)
     if nt == 64 and need <= 2:
         return 2
-    return 4 if need <= 4 else (8 if need <= 8 else 16)
+    return next(p for p in (4, 6, 8, 12, 16) if need <= p or p == 16)
 
 
 def candidates(nx: int) -> list[int]:

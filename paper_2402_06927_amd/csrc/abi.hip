@@ -12,6 +12,7 @@
 #include "filter.hpp"
 #include "model.hpp"
 #include "pcnl.hpp"
+#include "tiles.hpp"
 
 using namespace sch;
 
@@ -193,7 +194,7 @@ int launch_nudge_grad(const sch_model& md, const Tile& tl, const sch_obs& ob, in
   // threads with 8 nodes each at every grid measured, so a 16-node tile is
   // doubled where 512 threads allow it.  The Matern-noise kernels keep the
   // caller's tile, to which the noise operator's constants belong.
-  const Tile ta = (!M && tl.pmax == 16 && tl.nt <= 256) ? tile_for(md.nx, 2 * tl.nt) : tl;
+  const Tile ta = (!M && tl.pmax > 8 && tl.nt <= 256) ? tile_for(md.nx, 2 * tl.nt) : tl;
   const HelmConst K = make_helm(md, ta);
   return with_tile(ta, [&]<int PM, int NT, bool FULL>() -> int {
     if (M)
@@ -304,7 +305,10 @@ int launch_jitter(const sch_model& md, const Tile& tl, const sch_obs& ob, uint64
     // the workgroup's LDS (solver and window arrays plus the increments, here
     // counted twice: current and proposed) must fit the 160 KiB of a compute
     // unit; kStatic bounds the arrays' sizes from below, dyn's share covers the rest
-    constexpr size_t kStatic = 294 * sizeof(double) * (NT / kWave) + sizeof(AuxLds<PM, NT>);
+    // (and the arrays are taken as those of 8 or 16 slots: what is refused does
+    // not depend on how closely the slots fit the grid)
+    constexpr int PC = PM > 8 ? 16 : PM > 4 ? 8 : PM;
+    constexpr size_t kStatic = 294 * sizeof(double) * (NT / kWave) + sizeof(AuxLds<PC, NT>);
     static_assert(sizeof(RowLds<NT>) + sizeof(AuxLds<PM, NT>) <= 156 * 1024, "LDS");
     if (kStatic + 2 * dyn > 160 * 1024)
       return fail(SCH_E_SHAPE, "n_steps * n_modes too large for the jitter kernel at nx = %d",

@@ -469,7 +469,7 @@ struct LbfgsParams {
   double gtol, h0;
 };
 
-__device__ void lbfgs_direction(const LbfgsState& s, const LbfgsParams& P, int i) {
+static __device__ void lbfgs_direction(const LbfgsState& s, const LbfgsParams& P, int i) {
   const int Q = P.Q, M = P.mem;
   double* x = s.x + static_cast<size_t>(i) * Q;
   double* g = s.g + static_cast<size_t>(i) * Q;
@@ -543,7 +543,7 @@ __device__ void lbfgs_direction(const LbfgsState& s, const LbfgsParams& P, int i
 // stage's control without any step (the particle is inactive from the
 // start), kNudgeFromGiven starts the iteration at x0, kNudgeFromZero at 0.
 constexpr int kNudgeKeep = 0, kNudgeFromGiven = 1, kNudgeFromZero = 2;
-__global__ void k_lbfgs_init(LbfgsState s, LbfgsParams P, const double* x0, int x0_stride,
+static __global__ void k_lbfgs_init(LbfgsState s, LbfgsParams P, const double* x0, int x0_stride,
                              const int* mode = nullptr) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= P.n) return;
@@ -565,7 +565,7 @@ __global__ void k_lbfgs_init(LbfgsState s, LbfgsParams P, const double* x0, int 
   s.evals[i] = 0;
 }
 
-__global__ void k_lbfgs_update(LbfgsState s, LbfgsParams P) {
+static __global__ void k_lbfgs_update(LbfgsState s, LbfgsParams P) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= P.n || s.active[i] == 0) return;
   const int Q = P.Q, M = P.mem;
@@ -633,7 +633,7 @@ __global__ void k_lbfgs_update(LbfgsState s, LbfgsParams P) {
 // decisions; lane 0 writes the scalar state.  The steps and tests are those of
 // lbfgs_direction / k_lbfgs_update; only the summation order differs.
 // Returns whether the particle stays active.
-__device__ bool lbfgs_direction_w(const LbfgsState& s, const LbfgsParams& P, int i, int l,
+static __device__ bool lbfgs_direction_w(const LbfgsState& s, const LbfgsParams& P, int i, int l,
                                   int head, int count, int k, double f) {
   const int Q = P.Q, M = P.mem;
   double* x = s.x + static_cast<size_t>(i) * Q;
@@ -695,7 +695,7 @@ __device__ bool lbfgs_direction_w(const LbfgsState& s, const LbfgsParams& P, int
   return true;
 }
 
-__global__ void __launch_bounds__(256) k_lbfgs_update_w(LbfgsState s, LbfgsParams P) {
+static __global__ void __launch_bounds__(256) k_lbfgs_update_w(LbfgsState s, LbfgsParams P) {
   const int l = threadIdx.x & (kWave - 1);
   const int i = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
   if (i >= P.n || s.active[i] == 0) return;  // the whole wavefront
@@ -776,7 +776,7 @@ __global__ void __launch_bounds__(256) k_lbfgs_update_w(LbfgsState s, LbfgsParam
 
 // End of a stage: record the control of step n, the increment of the step
 // (dW^n + dLambda^n) for the advance, and the log Girsanov term.
-__global__ void k_nudge_commit(LbfgsState s, LbfgsParams P, int n_steps, int step,
+static __global__ void k_nudge_commit(LbfgsState s, LbfgsParams P, int n_steps, int step,
                                const double* dW, double* dLam, double* inc1, double* logG,
                                int* lbfgs_worst, int* iters, int* evals, double dt) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -796,13 +796,13 @@ __global__ void k_nudge_commit(LbfgsState s, LbfgsParams P, int n_steps, int ste
   evals[i] += s.evals[i];
 }
 
-__global__ void k_fill_i32(int* p, int v, int n) {
+static __global__ void k_fill_i32(int* p, int v, int n) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
     p[i] = v;
 }
 
 // status[i] keeps its first failure; tmp[i] is the status of the latest step.
-__global__ void k_status_merge(int* status, const int* tmp, int n) {
+static __global__ void k_status_merge(int* status, const int* tmp, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n && status[i] == SCH_OK) status[i] = tmp[i];
 }
@@ -810,7 +810,7 @@ __global__ void k_status_merge(int* status, const int* tmp, int n) {
 // Potential of a nudged particle for the tempered weights W~ (section 3.1.3):
 // J = phi - log G, +infinity where the nudged window failed or either term
 // is not finite.
-__global__ void k_nudged_potential(int n, const double* phi, const double* logG,
+static __global__ void k_nudged_potential(int n, const double* phi, const double* logG,
                                    const int* status, double* J) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;

@@ -57,7 +57,7 @@ struct BatchDev {
 
 // Forecast increments of every particle: counter (p, cycle * n_steps + n,
 // pair | FORECAST << 24, 0) under the instance's seed, as sch_draw_increments.
-__global__ void k_batch_draw(BatchDev B) {
+static __global__ void k_batch_draw(BatchDev B) {
   const int n_pairs = (B.n_modes + 1) / 2;
   const int64_t total = static_cast<int64_t>(B.G) * B.n_steps * n_pairs;
   const uint32_t step0 = *B.cycle * static_cast<uint32_t>(B.n_steps);
@@ -137,7 +137,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) k_
 
 // Negative log-likelihood of every particle against its instance's
 // observations of the current cycle (one wavefront per particle).
-__global__ void __launch_bounds__(kWave) k_batch_loglik(BatchDev B) {
+static __global__ void __launch_bounds__(kWave) k_batch_loglik(BatchDev B) {
   const int g = blockIdx.x;
   const InstDev& D = B.inst[B.pinst[g]];
   const int p = static_cast<int>(g - D.g0);
@@ -159,7 +159,7 @@ __global__ void __launch_bounds__(kWave) k_batch_loglik(BatchDev B) {
 
 // Per instance: weights from the carried log-weights and the likelihood,
 // ESS, and the resampling uniform (counter (0, cycle, RESAMPLE << 24, 0)).
-__global__ void __launch_bounds__(kTB) k_batch_weights(BatchDev B) {
+static __global__ void __launch_bounds__(kTB) k_batch_weights(BatchDev B) {
   __shared__ TemperLds L;
   const int i = blockIdx.x;
   const InstDev& D = B.inst[i];
@@ -172,7 +172,7 @@ __global__ void __launch_bounds__(kTB) k_batch_weights(BatchDev B) {
 
 // Per instance: systematic resampling when ESS < threshold (identity
 // indices otherwise).
-__global__ void __launch_bounds__(kTB) k_batch_resample(BatchDev B) {
+static __global__ void __launch_bounds__(kTB) k_batch_resample(BatchDev B) {
   __shared__ ResampleLds L;
   const int i = blockIdx.x;
   const InstDev& D = B.inst[i];
@@ -185,7 +185,7 @@ __global__ void __launch_bounds__(kTB) k_batch_resample(BatchDev B) {
 // p = state row idx[p] (phase 0), then back into the caller's arrays with the
 // log-weights reset (phase 1).  Instances that kept their particles are
 // skipped.
-__global__ void k_batch_gather(BatchDev B, int phase) {
+static __global__ void k_batch_gather(BatchDev B, int phase) {
   const int g = blockIdx.x;
   const int i = B.pinst[g];
   const InstDev& D = B.inst[i];
@@ -212,11 +212,11 @@ __global__ void k_batch_gather(BatchDev B, int phase) {
   }
 }
 
-__global__ void k_batch_next_cycle(unsigned int* cycle) {
+static __global__ void k_batch_next_cycle(unsigned int* cycle) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *cycle += 1u;
 }
 
-__global__ void k_fill_u32(unsigned int* p, unsigned int v, int n) {
+static __global__ void k_fill_u32(unsigned int* p, unsigned int v, int n) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = v;
 }
 

@@ -11,6 +11,7 @@
 #include "adjoint.hpp"
 #include "batch.hpp"
 #include "host.hpp"
+#include "tiles.hpp"
 
 struct sch_batch {
   int n_inst = 0, G = 0, n_steps = 0, n_modes = 0;
@@ -32,9 +33,10 @@ namespace {
 
 using namespace sch;
 
+constexpr size_t kMaxClasses = 32;  // four thread counts, five slot counts
 
 // Tile of one instance: the threads the caller asked for, else the model
-// calls' choice; nodes per thread 4, 8 or 16 (the batched kernels take
+// calls' choice; nodes per thread 4, 6, 8, 12 or 16 (the batched kernels take
 // ragged chunks, so a 2-slot choice runs on 4 slots).
 bool batch_tile(const sch_instance& in, Tile& tl) {
   if (in.threads == 0) {
@@ -68,7 +70,7 @@ Layout carve_batch(void* base, int n_inst, int64_t G, int n_steps, int n_modes, 
   L.inst = c.take<InstDev>(n_inst);
   L.pinst = c.take<int>(G);
   L.items = c.take<int>(G);
-  L.queues = c.take<unsigned int>(16);
+  L.queues = c.take<unsigned int>(kMaxClasses);
   L.cycle = c.take<unsigned int>(1);
   L.dW = c.take<double>(G * n_steps * n_modes);
   L.phi = c.take<double>(G);
@@ -115,12 +117,9 @@ int check_batch(const sch_batch_params* bp, int n_inst, const sch_instance* in, 
 
 template <class F>
 int with_batch_class(int nt, int pm, F&& f) {
-#define SCH_BCASE(NT_, PM_) \
+#define SCH_BCASE(PM_, NT_) \
   if (nt == NT_ && pm == PM_) return f.template operator()<PM_, NT_>();
-  SCH_BCASE(64, 4) SCH_BCASE(64, 8) SCH_BCASE(64, 16)
-  SCH_BCASE(128, 4) SCH_BCASE(128, 8) SCH_BCASE(128, 16)
-  SCH_BCASE(256, 4) SCH_BCASE(256, 8) SCH_BCASE(256, 16)
-  SCH_BCASE(512, 4) SCH_BCASE(512, 8) SCH_BCASE(512, 16)
+  SCH_BATCH_TILES(SCH_BCASE)
 #undef SCH_BCASE
   return fail(SCH_E_SHAPE, "no batched kernel for %d threads x %d nodes", nt, pm);
 }
@@ -257,7 +256,7 @@ int sch_batch_create(const sch_batch_params* bp, int32_t n_inst, const sch_insta
       ++k;
     }
     c.count = static_cast<int>(items.size()) - c.first;
-    if (b->classes.size() >= 16) {
+    if (b->classes.size() >= kMaxClasses) {
       delete b;
       return fail(SCH_E_SHAPE, "too many tile classes");
     }

@@ -270,7 +270,9 @@ __device__ __forceinline__ int wave_or(int v) {
 template <int NT>
 struct RowLds {
   static constexpr int W = NT / kWave;
-  alignas(16) double eq[4][NT];  // interface equations (A, B, C, R), one per chunk
+  // interface equations (A, B, C, R), one per chunk (on one wavefront they stay
+  // in its lanes)
+  alignas(16) double eq[4][NT > kWave ? NT : 2];
   double etail[3][W];          // last-row spike values of each wavefront's last chunk
   double edge[2][W][6];        // wavefront edge values of halo exchanges, double buffered
   double red[3][W];            // workgroup reductions
@@ -304,12 +306,12 @@ __device__ __forceinline__ Chunk chunk_of(int nx, int t) {
 }
 
 // Rows every chunk holds: chunk_of deals nx / NT or nx / NT + 1 rows, and the
-// tiles (tile_for) take 8 slots only when nx > 4 NT, 16 only when nx > 8 NT,
-// and always nx >= NT; the host refuses a tile that breaks this.  Slots below
-// kMinRows are live in every chunk, so the masks of ragged chunks start there
-// (compile-time true below it).
+// tiles (tile_for) take 6 slots only when nx > 4 NT, 8 when nx > 6 NT, 12 when
+// nx > 8 NT, 16 when nx > 12 NT, and always nx >= NT; the host refuses a tile
+// that breaks this.  Slots below kMinRows are live in every chunk, so the masks
+// of ragged chunks start there (compile-time true below it).
 template <int PMAX>
-inline constexpr int kMinRows = PMAX >= 8 ? PMAX / 2 : 1;
+inline constexpr int kMinRows = PMAX >= 12 ? PMAX - 4 : PMAX >= 6 ? PMAX - 2 : 1;
 template <int PMAX, bool FULL>
 __device__ __forceinline__ bool slot_live(int j, int cnt) {
   return FULL || j < kMinRows<PMAX> || j < cnt;

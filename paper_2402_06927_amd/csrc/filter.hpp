@@ -7,7 +7,7 @@
 namespace sch {
 
 // dW[p][n][q] = sqrt(dt) z, one Philox block per (particle, step, mode pair).
-__global__ void k_draw_increments(uint64_t seed, uint32_t step0, uint32_t tag, uint32_t word3,
+static __global__ void k_draw_increments(uint64_t seed, uint32_t step0, uint32_t tag, uint32_t word3,
                                   int n_particles, int n_steps, int n_modes, double sdt,
                                   double* dW) {
   const int n_pairs = (n_modes + 1) / 2;
@@ -28,7 +28,7 @@ __global__ void k_draw_increments(uint64_t seed, uint32_t step0, uint32_t tag, u
 }
 
 // Raw Philox blocks: out[i] = philox(ctr[i], seed).
-__global__ void k_philox_blocks(uint64_t seed, int n, const uint32_t* ctr, uint32_t* out) {
+static __global__ void k_philox_blocks(uint64_t seed, int n, const uint32_t* ctr, uint32_t* out) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
     const Ctr4 r = philox10(Ctr4{{ctr[4 * i], ctr[4 * i + 1], ctr[4 * i + 2], ctr[4 * i + 3]}}, seed);
 #pragma unroll
@@ -40,7 +40,7 @@ __global__ void k_philox_blocks(uint64_t seed, int n, const uint32_t* ctr, uint3
 // sqrt(dt) z with z from the PCN-tagged block (p, step0 + n, pair | tag << 24,
 // word3 | j), and the acceptance uniform vacc[j][p] from the ACCEPT-tagged
 // block (p, cycle, tag << 24, word3 | j).
-__global__ void k_draw_pcn(uint64_t seed, uint32_t step0, uint32_t cycle, uint32_t word3,
+static __global__ void k_draw_pcn(uint64_t seed, uint32_t step0, uint32_t cycle, uint32_t word3,
                            int n_jitter, int n_particles, int n_steps, int n_modes, double sdt,
                            double* zeta, double* vacc) {
   const int n_pairs = (n_modes + 1) / 2;
@@ -68,7 +68,7 @@ __global__ void k_draw_pcn(uint64_t seed, uint32_t step0, uint32_t cycle, uint32
 }
 
 // One uniform in [0,1) into a device scalar.
-__global__ void k_draw_uniform(uint64_t seed, uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
+static __global__ void k_draw_uniform(uint64_t seed, uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                double* out) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *out = uniform1(seed, c0, c1, c2, c3);
 }
@@ -82,7 +82,7 @@ __device__ __forceinline__ double p1_at(const double* u, int nx, int n_obs, int 
   return (1.0 - r) * u[e] + r * u[e1];
 }
 
-__global__ void __launch_bounds__(kWave) k_observe(int nx, int n_obs, const double* u,
+static __global__ void __launch_bounds__(kWave) k_observe(int nx, int n_obs, const double* u,
                                                    double* out) {
   const int p = blockIdx.x;
   const double* up = u + static_cast<size_t>(p) * nx;
@@ -90,7 +90,7 @@ __global__ void __launch_bounds__(kWave) k_observe(int nx, int n_obs, const doub
     out[static_cast<size_t>(p) * n_obs + j] = p1_at(up, nx, n_obs, j);
 }
 
-__global__ void __launch_bounds__(kWave) k_loglik(int nx, int n_obs, const double* u,
+static __global__ void __launch_bounds__(kWave) k_loglik(int nx, int n_obs, const double* u,
                                                   const double* y, const double* sigma,
                                                   double* phi) {
   const int p = blockIdx.x;
@@ -218,7 +218,7 @@ __device__ void temper_body(int n, const double* phi, const double* extra, doubl
   }
 }
 
-__global__ void __launch_bounds__(kTB) k_temper(int n, const double* phi, const double* extra,
+static __global__ void __launch_bounds__(kTB) k_temper(int n, const double* phi, const double* extra,
                                                 double* theta_io, double thr, int n_bisect,
                                                 double* dtheta_out, double* w, double* logw_out,
                                                 double* ess_out) {
@@ -326,7 +326,7 @@ __device__ void resample_body(int n, const double* w, const double* u0p, const d
   }
 }
 
-__global__ void __launch_bounds__(kTB) k_resample(int n, const double* w, const double* u0p,
+static __global__ void __launch_bounds__(kTB) k_resample(int n, const double* w, const double* u0p,
                                                   const double* cond_ess, double cond_thr,
                                                   int* idx, int* degenerate,
                                                   unsigned long long* cum) {
@@ -335,7 +335,7 @@ __global__ void __launch_bounds__(kTB) k_resample(int n, const double* w, const 
 }
 
 // dst[j][:] = src[idx[j]][:]
-__global__ void k_gather(int n_rows, int64_t row_len, const int* idx, const double* src,
+static __global__ void k_gather(int n_rows, int64_t row_len, const int* idx, const double* src,
                          double* dst) {
   const int j = blockIdx.y;
   const int r = idx[j];
@@ -351,7 +351,7 @@ __global__ void k_gather(int n_rows, int64_t row_len, const int* idx, const doub
 // Ensemble statistics of section 4 (EMRE, RB, RES) against a truth row.
 // ---------------------------------------------------------------------------
 // mean[i] = (1/n) sum_p u[p][i]
-__global__ void k_ens_mean(int n, int nx, const double* u, double* mean) {
+static __global__ void k_ens_mean(int n, int nx, const double* u, double* mean) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nx; i += gridDim.x * blockDim.x) {
     double acc = 0.0;
     for (int p = 0; p < n; ++p) acc += u[static_cast<size_t>(p) * nx + i];
@@ -360,7 +360,7 @@ __global__ void k_ens_mean(int n, int nx, const double* u, double* mean) {
 }
 
 // Per particle (one wavefront each): |ua - u_p|^2 and |u_p - mean|^2.
-__global__ void __launch_bounds__(kWave) k_ens_norms(int nx, const double* u, const double* ua,
+static __global__ void __launch_bounds__(kWave) k_ens_norms(int nx, const double* u, const double* ua,
                                                      const double* mean, double* sq) {
   const int p = blockIdx.x;
   const double* up = u + static_cast<size_t>(p) * nx;
@@ -379,7 +379,7 @@ __global__ void __launch_bounds__(kWave) k_ens_norms(int nx, const double* u, co
 }
 
 // out = (EMRE, RB, RES) from the per-particle squares (one wavefront).
-__global__ void __launch_bounds__(kWave) k_ens_final(int n, int nx, const double* ua,
+static __global__ void __launch_bounds__(kWave) k_ens_final(int n, int nx, const double* ua,
                                                      const double* mean, const double* sq,
                                                      double* out) {
   double na = 0.0, nb = 0.0, se = 0.0, ss = 0.0;
@@ -406,19 +406,19 @@ __global__ void __launch_bounds__(kWave) k_ens_final(int n, int nx, const double
 
 // A particle whose window failed (status != SCH_OK) gets phi = +inf: zero
 // weight, so the next resampling replaces it.
-__global__ void k_mask_failed(int n, const int* status, double* phi) {
+static __global__ void k_mask_failed(int n, const int* status, double* phi) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n && status[i] != SCH_OK) phi[i] = INFINITY;
 }
 
-__global__ void k_fill(double* p, double v, int64_t n) {
+static __global__ void k_fill(double* p, double v, int64_t n) {
   for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x)
     p[i] = v;
 }
 
 // *out += sum of a[0 .. n) (one workgroup of 256 threads).
-__global__ void __launch_bounds__(256) k_sum_i32_u64(int n, const int* a,
+static __global__ void __launch_bounds__(256) k_sum_i32_u64(int n, const int* a,
                                                      unsigned long long* out) {
   __shared__ unsigned long long part[256];
   unsigned long long s = 0;
@@ -432,7 +432,7 @@ __global__ void __launch_bounds__(256) k_sum_i32_u64(int n, const int* a,
   if (threadIdx.x == 0) *out += part[0];
 }
 
-__global__ void k_zero_u64(unsigned long long* p, int n) {
+static __global__ void k_zero_u64(unsigned long long* p, int n) {
   for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0ull;
 }
 

@@ -9,6 +9,7 @@
 #include <string>
 
 #include "helm.hpp"
+#include "tile_list.hpp"
 
 namespace sch {
 
@@ -50,22 +51,32 @@ struct Tile {
   bool full;
 };
 
-// Slots per thread: 4, 8 or 16, and 2 on a single wavefront (nx <= 128),
-// where the chunk sweeps would otherwise carry masked slots beside one or two
-// rows.
+// Slots per thread: 4, 6, 8, 12 or 16, and 2 on a single wavefront (nx <= 128).
+// A slot that no chunk holds costs what a live one does, and one that not
+// every chunk holds costs selects besides: with 8 and 16 slots alone a
+// window's step took 36.9 us instead of 28.7 at 1500 nodes (128 threads, 1024
+// particles), 72.6 instead of 54.1 at 3000 (256 threads).
 inline Tile tile_for(int nx, int nt) {
   Tile tl{};
   tl.nt = nt;
   const int need = (nx + nt - 1) / nt;
-  tl.pmax = (nt == 64 && need <= 2) ? 2 : need <= 4 ? 4 : (need <= 8 ? 8 : 16);
-  tl.full = (nx % nt == 0) && (nx / nt == tl.pmax);
+  tl.pmax = (nt == 64 && need <= 2) ? 2
+            : need <= 4             ? 4
+            : need <= 6             ? 6
+            : need <= 8             ? 8
+            : need <= 12            ? 12
+                                    : 16;
+  // 6 and 12 slots are for ragged grids: they have no kernels of their own for
+  // grids that fill them (masks that are always true cost less than the
+  // kernels' build)
+  tl.full = (nx % nt == 0) && (nx / nt == tl.pmax) && (tl.pmax & (tl.pmax - 1)) == 0;
   return tl;
 }
 
 // The kernels take every chunk to hold at least kMinRows<PMAX> rows (their
-// ragged-chunk masks start there): PMAX / 2 for 8 and 16 slots, else 1.
+// ragged-chunk masks start there).
 inline bool tile_rows_ok(int nx, const Tile& tl) {
-  const int min_rows = tl.pmax >= 8 ? tl.pmax / 2 : 1;
+  const int min_rows = tl.pmax >= 12 ? tl.pmax - 4 : tl.pmax >= 6 ? tl.pmax - 2 : 1;
   return nx / tl.nt >= min_rows && (nx + tl.nt - 1) / tl.nt <= tl.pmax;
 }
 
@@ -129,20 +140,10 @@ inline HelmConst make_helm(const sch_model& md, const Tile& tl) {
 
 template <class F>
 inline int with_tile(const Tile& tl, F&& f) {
-#define SCH_CASE(NT_, PM_)                                                       \
-  if (tl.nt == NT_ && tl.pmax == PM_)                                            \
-    return tl.full ? f.template operator()<PM_, NT_, true>()                     \
-                   : f.template operator()<PM_, NT_, false>();
-  SCH_CASE(64, 2)
-  SCH_CASE(64, 4)
-  SCH_CASE(64, 8)
-  SCH_CASE(64, 16)
-  SCH_CASE(128, 8)
-  SCH_CASE(128, 16)
-  SCH_CASE(256, 8)
-  SCH_CASE(256, 16)
-  SCH_CASE(512, 8)
-  SCH_CASE(512, 16)
+#define SCH_CASE(PM_, NT_, FULL_)                                    \
+  if (tl.nt == NT_ && tl.pmax == PM_ && tl.full == FULL_)            \
+    return f.template operator()<PM_, NT_, FULL_>();
+  SCH_TILES(SCH_CASE)
 #undef SCH_CASE
   return fail(SCH_E_SHAPE, "no kernel for %d threads x %d nodes", tl.nt, tl.pmax);
 }

@@ -135,7 +135,7 @@ __device__ __forceinline__ void gemm_store(const GemmArgs& g, int m0, int n0, in
 // 256 threads = 4 wavefronts, each computing a 32 x 32 block as 2 x 2 matrix-
 // core tiles of 16 x 16; K advances in chunks of 32 staged in LDS.  Element-
 // wise loads: any operand layout with one unit stride.
-__global__ void __launch_bounds__(256) k_gemm_bf16(const GemmArgs g) {
+static __global__ void __launch_bounds__(256) k_gemm_bf16(const GemmArgs g) {
   __shared__ __attribute__((aligned(16))) uint16_t As[kGM][kGK + kGPad];
   __shared__ __attribute__((aligned(16))) uint16_t Bs[kGN][kGK + kGPad];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
@@ -412,7 +412,7 @@ __global__ void __launch_bounds__(256) k_gemm_bf16_lds(const GemmArgs g) {
 // The sum of the nz split-K slices of a K-contiguous loader (in slice order), then
 // the epilogue, one element per thread (consecutive elements across lanes, so
 // the epilogue's stores coalesce).
-__global__ void k_gemm_reduce(const GemmArgs g, int nz) {
+static __global__ void k_gemm_reduce(const GemmArgs g, int nz) {
   const int64_t mn = static_cast<int64_t>(g.M) * g.N;
   for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < mn;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
@@ -424,7 +424,7 @@ __global__ void k_gemm_reduce(const GemmArgs g, int nz) {
 
 // Mean-squared error of Y against T ([rows][cols]) and its gradient
 // dY = 2 (Y - T) / (rows cols) (float32 and bfloat16); *loss accumulates.
-__global__ void k_mse(int64_t n, const float* Y, const float* T, float inv_count, float* dY32,
+static __global__ void k_mse(int64_t n, const float* Y, const float* T, float inv_count, float* dY32,
                       uint16_t* dY16, double* loss) {
   double acc = 0.0;
   for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
@@ -462,7 +462,7 @@ struct ColsumBatch {
   float* out[kColsumBatch];
 };
 
-__global__ void __launch_bounds__(256) k_colsum_part(int rows, const ColsumBatch b,
+static __global__ void __launch_bounds__(256) k_colsum_part(int rows, const ColsumBatch b,
                                                      double* part) {
   __shared__ double red[4][64];
   int k = 0;
@@ -481,7 +481,7 @@ __global__ void __launch_bounds__(256) k_colsum_part(int rows, const ColsumBatch
         ((red[0][cl] + red[1][cl]) + red[2][cl]) + red[3][cl];
 }
 
-__global__ void k_colsum_final(int n_part, const ColsumBatch b, const double* part) {
+static __global__ void k_colsum_final(int n_part, const ColsumBatch b, const double* part) {
   const int c = blockIdx.x * blockDim.x + threadIdx.x, ctot = b.coff[b.n];
   if (c >= ctot) return;
   int k = 0;
@@ -505,7 +505,7 @@ struct TransposeBatch {
   uint16_t* out[kTransposeBatch];
 };
 
-__global__ void __launch_bounds__(256) k_transpose_bf16(const TransposeBatch b) {
+static __global__ void __launch_bounds__(256) k_transpose_bf16(const TransposeBatch b) {
   __shared__ uint16_t tile[64][66];
   int k = 0;
   while (k + 1 < b.n && static_cast<int>(blockIdx.x) >= b.tile0[k + 1]) ++k;
@@ -528,7 +528,7 @@ __global__ void __launch_bounds__(256) k_transpose_bf16(const TransposeBatch b) 
 
 // Column means and standard deviations (two passes, float64 accumulation);
 // a column whose deviation is below 1e-12 gets deviation 1.
-__global__ void k_colstats(int rows, int cols, const float* A, float* mean, float* sdev) {
+static __global__ void k_colstats(int rows, int cols, const float* A, float* mean, float* sdev) {
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= cols) return;
   double s = 0.0;
@@ -580,7 +580,7 @@ __device__ __forceinline__ int64_t weight_slot(const MlpDims& d, int64_t i) {
 // corrections c1 = 1 / (1 - beta1^t), c2 = 1 / (1 - beta2^t) given by the
 // caller; refreshes the bfloat16 weight copy.  With grad == nullptr only the
 // copy is refreshed.
-__global__ void k_adam(MlpDims d, float* p, const float* grad, float* m, float* v, float lr,
+static __global__ void k_adam(MlpDims d, float* p, const float* grad, float* m, float* v, float lr,
                        float beta1, float beta2, float eps, float c1, float c2, uint16_t* wb) {
   for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < d.n_params;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
@@ -604,7 +604,7 @@ __global__ void k_adam(MlpDims d, float* p, const float* grad, float* m, float* 
 // (nx values), standardised with the training means and deviations and
 // rounded to bfloat16.  raw (float32, optional) receives the unscaled values,
 // misfit (optional) the Euclidean norm of y - P u.  One workgroup per particle.
-__global__ void k_mlp_features(int nx, int n_obs, const double* u, const double* y,
+static __global__ void k_mlp_features(int nx, int n_obs, const double* u, const double* y,
                                const float* mean, const float* sdev, uint16_t* X, float* raw,
                                double* misfit) {
   const int p = blockIdx.x, F = n_obs + nx;
@@ -639,7 +639,7 @@ __global__ void k_mlp_features(int nx, int n_obs, const double* u, const double*
 
 // Stored raw features to network inputs: X = bf16((raw - mean) / sdev), the
 // same arithmetic as the scaling path of k_mlp_features.
-__global__ void k_mlp_encode(int64_t n, int cols, const float* raw, const float* mean,
+static __global__ void k_mlp_encode(int64_t n, int cols, const float* raw, const float* mean,
                              const float* sdev, uint16_t* X) {
   for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
@@ -650,7 +650,7 @@ __global__ void k_mlp_encode(int64_t n, int cols, const float* raw, const float*
 
 // Training targets: T = (dLambda - mean) / sdev in float32 (raw float32 copy
 // of dLambda in `raw` when mean is null).
-__global__ void k_mlp_targets(int64_t n, int cols, const double* dLam, const float* mean,
+static __global__ void k_mlp_targets(int64_t n, int cols, const double* dLam, const float* mean,
                               const float* sdev, float* out) {
   for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
@@ -665,7 +665,7 @@ __global__ void k_mlp_targets(int64_t n, int cols, const double* dLam, const flo
 // mode (optional): per particle, keep_mode where the prediction is used and
 // fallback_mode where the misfit is above the threshold (the start modes of
 // sch_pf_nudged_cycle_warm).
-__global__ void k_mlp_controls(int64_t n, int cols, const float* Y, const float* mean,
+static __global__ void k_mlp_controls(int64_t n, int cols, const float* Y, const float* mean,
                                const float* sdev, const double* misfit, double threshold,
                                double* dLam, int* mode, int keep_mode, int fallback_mode) {
   for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;

@@ -95,6 +95,7 @@ __device__ __forceinline__ int stage_pos(int i) { return i ^ ((i >> 5) & 15); }
 template <int PMAX, bool FULL>
 __device__ __forceinline__ double staged_slot(const double* stg, const Chunk& ch, int t, int j) {
   if constexpr (FULL) {
+    static_assert((PMAX & (PMAX - 1)) == 0, "the slot index has bits of its own");
     // start = PMAX t: the exclusive-or touches the low bits only, where the
     // slot index sits
     const int b = 8 * stage_pos(PMAX * t);

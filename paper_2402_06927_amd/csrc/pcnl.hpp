@@ -15,14 +15,14 @@
 namespace sch {
 
 // g -= x / dt: the adjoint's gradient without the Girsanov term.
-__global__ void k_pcnl_grad(int64_t total, double idt, const double* x, double* g) {
+static __global__ void k_pcnl_grad(int64_t total, double idt, const double* x, double* g) {
   for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < total;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x)
     g[i] -= x[i] * idt;
 }
 
 // v = rho x + srho zeta - c theta g, zeta = sqrt(dt) z, c = (1 - rho) dt.
-__global__ void k_pcnl_propose(int64_t total, double rho, double srho, double c,
+static __global__ void k_pcnl_propose(int64_t total, double rho, double srho, double c,
                                const double* theta, const double* x, const double* g,
                                const double* zeta, double* v) {
   const double ct = c * *theta;
@@ -38,7 +38,7 @@ __global__ void k_pcnl_propose(int64_t total, double rho, double srho, double c,
 // log q(x -> v) = -|v - rho x + c theta g(x)|^2 / (2 (1 - rho^2) dt).  A state
 // whose window failed (phi = inf) is left for any finite proposal.  On
 // acceptance x, g(x) and phi take the proposal's values.
-__global__ void __launch_bounds__(kWave) k_pcnl_accept(int d, double rho, double dt,
+static __global__ void __launch_bounds__(kWave) k_pcnl_accept(int d, double rho, double dt,
                                                        const double* theta, const double* vacc,
                                                        const int* status, const double* Jv,
                                                        double* x, double* gx, double* phi,
@@ -106,7 +106,7 @@ __global__ void __launch_bounds__(kWave) k_pcnl_accept(int d, double rho, double
 // evaluation (that step's closing half kick, then this step's opening one).
 // Then the rotation by h (c = cos h, s = sin h) into (xp, v).  A particle
 // whose last evaluation failed is marked in bad.  a = (h/2) dt.
-__global__ void k_hmc_step(int64_t total, int d, int first, double a, const double* theta,
+static __global__ void k_hmc_step(int64_t total, int d, int first, double a, const double* theta,
                            double c, double s, const double* x, const double* gx,
                            const double* zeta, double* xp, double* v, const double* gp,
                            const int* status, int* bad) {
@@ -138,7 +138,7 @@ __global__ void k_hmc_step(int64_t total, int d, int first, double a, const doub
 // H(x, v) = theta phi(x) + (|x|^2 + |v|^2) / (2 dt).  A trajectory with a
 // failed evaluation is rejected; a failed current state is left for any
 // finite proposal.  On acceptance x, gx and phi take the proposal's values.
-__global__ void __launch_bounds__(kWave) k_hmc_accept(int d, double a, double dt,
+static __global__ void __launch_bounds__(kWave) k_hmc_accept(int d, double a, double dt,
                                                       const double* theta, const double* vacc,
                                                       const int* status, const int* bad,
                                                       const double* Jp, double* x, double* gx,
