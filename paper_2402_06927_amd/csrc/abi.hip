@@ -713,7 +713,7 @@ int sch_ensemble_step(const sch_model* md, int32_t n, int32_t n_steps, double* m
                       const double* dW, const double* dLam, int32_t* status, int32_t* iters,
                       void* stream) {
   Tile tl;
-  if (int rc = check_model(md, tl)) return rc;
+  if (int rc = check_model(md, tl, n)) return rc;
   if (n < 1 || n_steps < 0 || !m || !u || !dW) return fail(SCH_E_ARG, "bad arguments to sch_ensemble_step");
   if (n_steps == 0) return SCH_OK;
   return launch_window(*md, tl, n, n_steps, m, u, dW, dLam, status, iters, nullptr, S(stream));
@@ -776,7 +776,7 @@ static int check_jitter_args(const sch_model* md, const sch_obs* ob, const sch_r
                              const double* dW, const double* phi, const double* m_end,
                              const double* u_end, const double* theta, double rho,
                              int32_t n_jitter, Tile& tl, const char* who) {
-  if (int rc = check_model(md, tl)) return rc;
+  if (int rc = check_model(md, tl, n)) return rc;
   if (int rc = check_obs(ob)) return rc;
   if (!rng || n < 1 || n_steps < 1 || !m0 || !u0 || !dW || !phi || !m_end || !u_end || !theta ||
       !(rho >= 0 && rho <= 1) || n_jitter < 0)
@@ -1078,7 +1078,7 @@ int sch_pf_bootstrap_cycle(const sch_model* md, const sch_obs* ob, uint64_t seed
                            double* logw, void* workspace, sch_cycle_stats* stats,
                            void* stream) {
   Tile tl;
-  if (int rc = check_model(md, tl)) return rc;
+  if (int rc = check_model(md, tl, n)) return rc;
   if (int rc = check_obs(ob)) return rc;
   if (n < 1 || n > 65535 || n_steps < 1 || !m || !u || !logw || !workspace || !stats)
     return fail(SCH_E_ARG, "bad arguments to sch_pf_bootstrap_cycle");
@@ -1091,7 +1091,7 @@ int sch_pf_tempered_cycle(const sch_model* md, const sch_obs* ob, uint64_t seed,
                           int32_t n_jitter, int32_t max_temper, double* m, double* u,
                           void* workspace, sch_cycle_stats* stats, void* stream) {
   Tile tl;
-  if (int rc = check_model(md, tl)) return rc;
+  if (int rc = check_model(md, tl, n)) return rc;
   if (int rc = check_obs(ob)) return rc;
   if (n < 1 || n > 65535 || n_steps < 1 || !m || !u || !workspace || !stats || n_bisect < 0 ||
       max_temper < 1 || !(rho >= 0 && rho <= 1) || n_jitter < 0)
@@ -1212,7 +1212,7 @@ int sch_pf_nudged_cycle(const sch_model* md, const sch_obs* ob, uint64_t seed, u
                         int32_t ckpt_every, double* m, double* u, double* dLambda,
                         void* workspace, sch_cycle_stats* stats, void* stream) {
   Tile tl;
-  if (int rc = check_model(md, tl)) return rc;
+  if (int rc = check_model(md, tl, n)) return rc;
   if (int rc = check_obs(ob)) return rc;
   if (n < 1 || n > 65535 || n_steps < 1 || !m || !u || !dLambda || !workspace || !stats ||
       !opts || n_bisect < 0 || max_temper < 1 || !(rho >= 0 && rho <= 1) || n_jitter < 0 ||
@@ -1230,7 +1230,7 @@ int sch_pf_nudged_cycle_warm(const sch_model* md, const sch_obs* ob, uint64_t se
                              double* dLambda, const int32_t* mode, void* workspace,
                              sch_cycle_stats* stats, void* stream) {
   Tile tl;
-  if (int rc = check_model(md, tl)) return rc;
+  if (int rc = check_model(md, tl, n)) return rc;
   if (int rc = check_obs(ob)) return rc;
   if (n < 1 || n > 65535 || n_steps < 1 || !m || !u || !dLambda || !mode || !workspace ||
       !stats || !opts || n_bisect < 0 || max_temper < 1 || !(rho >= 0 && rho <= 1) ||
@@ -1264,7 +1264,7 @@ int sch_ensemble_step_matern(const sch_model* md, const sch_matern* mt, int32_t 
                              int32_t n_steps, double* m, double* u, const double* dWc,
                              int32_t* status, int32_t* iters, void* stream) {
   Tile tl;
-  if (int rc = check_model(md, tl)) return rc;
+  if (int rc = check_model(md, tl, n)) return rc;
   MaternDev M;
   if (int rc = make_matern(*md, mt, tl, M)) return rc;
   if (n < 1 || n > 65535 || n_steps < 0 || !m || !u || !dWc)
@@ -1358,7 +1358,7 @@ int jitter_matern(const sch_model* md, const sch_matern* mt, const sch_obs* ob,
                   const double* theta, double rho, int32_t n_jitter, int32_t* n_accept,
                   void* workspace, void* stream, const double* dLamc) {
   Tile tl;
-  if (int rc = check_model(md, tl)) return rc;
+  if (int rc = check_model(md, tl, n)) return rc;
   if (int rc = check_obs(ob)) return rc;
   MaternDev M;
   if (int rc = make_matern(*md, mt, tl, M)) return rc;
@@ -1402,7 +1402,7 @@ int sch_pf_bootstrap_cycle_matern(const sch_model* md, const sch_matern* mt, con
                                   double ess_frac, double* m, double* u, double* logw,
                                   void* workspace, sch_cycle_stats* stats, void* stream) {
   Tile tl;
-  if (int rc = check_model(md, tl)) return rc;
+  if (int rc = check_model(md, tl, n)) return rc;
   if (int rc = check_obs(ob)) return rc;
   MaternDev M;
   if (int rc = make_matern(*md, mt, tl, M)) return rc;
@@ -1433,7 +1433,7 @@ int sch_jitter_pcnl(const sch_model* md, const sch_obs* ob, const sch_rng* rng, 
                     int32_t n_jitter, int32_t ckpt_every, int32_t* n_accept, void* workspace,
                     void* stream) {
   Tile tl;
-  if (int rc = check_model(md, tl)) return rc;
+  if (int rc = check_model(md, tl, n)) return rc;
   if (int rc = check_obs(ob)) return rc;
   if (!rng || n < 1 || n > 65535 || n_steps < 1 || !m0 || !u0 || !dW || !phi || !m_end ||
       !u_end || !theta || !(rho >= 0 && rho < 1) || n_jitter < 0 || ckpt_every < 1 ||
@@ -1503,7 +1503,7 @@ int sch_pf_tempered_cycle_pcnl(const sch_model* md, const sch_obs* ob, uint64_t 
                                int32_t ckpt_every, double* m, double* u, void* workspace,
                                sch_cycle_stats* stats, void* stream) {
   Tile tl;
-  if (int rc = check_model(md, tl)) return rc;
+  if (int rc = check_model(md, tl, n)) return rc;
   if (int rc = check_obs(ob)) return rc;
   if (n < 1 || n > 65535 || n_steps < 1 || !m || !u || !workspace || !stats || n_bisect < 0 ||
       max_temper < 1 || !(rho >= 0 && rho < 1) || n_jitter < 0 || ckpt_every < 1)
@@ -1537,7 +1537,7 @@ int sch_jitter_hmc(const sch_model* md, const sch_obs* ob, const sch_rng* rng, i
                    int32_t n_jitter, int32_t ckpt_every, int32_t* n_accept, void* workspace,
                    void* stream) {
   Tile tl;
-  if (int rc = check_model(md, tl)) return rc;
+  if (int rc = check_model(md, tl, n)) return rc;
   if (int rc = check_obs(ob)) return rc;
   if (!rng || n < 1 || n > 65535 || n_steps < 1 || !m0 || !u0 || !dW || !phi || !m_end ||
       !u_end || !theta || !hmc_ok(h, n_leap) || n_jitter < 0 || ckpt_every < 1 ||
@@ -1558,7 +1558,7 @@ int sch_pf_tempered_cycle_hmc(const sch_model* md, const sch_obs* ob, uint64_t s
                               int32_t max_temper, int32_t ckpt_every, double* m, double* u,
                               void* workspace, sch_cycle_stats* stats, void* stream) {
   Tile tl;
-  if (int rc = check_model(md, tl)) return rc;
+  if (int rc = check_model(md, tl, n)) return rc;
   if (int rc = check_obs(ob)) return rc;
   if (n < 1 || n > 65535 || n_steps < 1 || !m || !u || !workspace || !stats || n_bisect < 0 ||
       max_temper < 1 || !hmc_ok(h, n_leap) || n_jitter < 0 || ckpt_every < 1)
@@ -1607,7 +1607,7 @@ int sch_pf_tempered_cycle_matern(const sch_model* md, const sch_matern* mt, cons
                                  int32_t max_temper, double* m, double* u, void* workspace,
                                  sch_cycle_stats* stats, void* stream) {
   Tile tl;
-  if (int rc = check_model(md, tl)) return rc;
+  if (int rc = check_model(md, tl, n)) return rc;
   if (int rc = check_obs(ob)) return rc;
   MaternDev M;
   if (int rc = make_matern(*md, mt, tl, M)) return rc;

@@ -36,11 +36,11 @@ using namespace sch;
 constexpr size_t kMaxClasses = 32;  // four thread counts, five slot counts
 
 // Tile of one instance: the threads the caller asked for, else the model
-// calls' choice; nodes per thread 4, 6, 8, 12 or 16 (the batched kernels take
+// calls' choice for the G particles of all instances; nodes per thread 4, 6, 8, 12 or 16 (the batched kernels take
 // ragged chunks, so a 2-slot choice runs on 4 slots).
-bool batch_tile(const sch_instance& in, Tile& tl) {
+bool batch_tile(const sch_instance& in, Tile& tl, int64_t G) {
   if (in.threads == 0) {
-    if (!pick_tile(in.nx, tl)) return false;
+    if (!pick_tile(in.nx, tl, G)) return false;
   } else {
     const int nt = in.threads;
     if (nt < 64 || nt > 512 || (nt & (nt - 1)) != 0 || in.nx < nt || (in.nx + nt - 1) / nt > 16)
@@ -105,7 +105,7 @@ int check_batch(const sch_batch_params* bp, int n_inst, const sch_instance* in, 
     if (s.nx < 64 || s.nx > 8192 || s.n_particles < 1 || s.n_particles > 65536)
       return fail(SCH_E_SHAPE, "instance %d: nx = %d, n = %d not supported", i, s.nx,
                   s.n_particles);
-    if (!batch_tile(s, tl))
+    if (!batch_tile(s, tl, 1))
       return fail(SCH_E_SHAPE, "instance %d: no tile for nx = %d with %d threads", i, s.nx,
                   s.threads);
     G += s.n_particles;
@@ -205,7 +205,7 @@ int sch_batch_create(const sch_batch_params* bp, int32_t n_inst, const sch_insta
   int64_t g0 = 0, s0 = 0;
   for (int i = 0; i < n_inst; ++i) {
     const sch_instance& s = in[i];
-    batch_tile(s, tiles[i]);
+    batch_tile(s, tiles[i], G);
     sch_model md{bp->L, bp->alpha, bp->mu, bp->dt, s.nx, bp->n_modes, s.xi, bp->picard_tol,
                  bp->picard_max};
     InstDev& D = inst[i];

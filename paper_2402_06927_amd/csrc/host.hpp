@@ -45,7 +45,8 @@ inline int grid_for(int64_t work, int block) {
 // ---------------------------------------------------------------------------
 // Tile choice: NT threads per particle (power of two, 64..512), each holding
 // up to PMAX consecutive nodes in registers (tile_for).  By default NT is the smallest
-// power of two with nx / NT <= 8; SCH_TUNE_THREADS overrides it.
+// power of two with nx / NT <= 8, or half of it (pick_tile); SCH_TUNE_THREADS
+// overrides it.
 struct Tile {
   int nt, pmax;
   bool full;
@@ -82,13 +83,24 @@ inline bool tile_rows_ok(int nx, const Tile& tl) {
 
 inline int g_tune_threads = 0;  // SCH_TUNE_THREADS
 
-inline bool pick_tile(int nx, Tile& tl) {
+// n: the particles that the call advances, 0 if its kernels take the tile for
+// short chunks whatever their number.  Twice the nodes a thread cost less a
+// node (fewer chunks to join, fewer barriers) but keep a particle longer: they
+// pay once the short chunks' workgroups wait for a place (window, us a step,
+// short / long chunks: 2048 nodes 18.5 / 23.5 at 512 particles, 33.2 / 27.2 at
+// 1024; 1000 nodes 13.6 / 15.8 at 256, 19.0 / 17.0 at 512), at two wavefronts a
+// particle earlier, since one wavefront needs no barriers at all, and at
+// eight always (3000 nodes 18.4 / 17.5 at 32 particles, 77.8 / 54.1 at 1024;
+// 4096 nodes 16.7 / 16.7 and 72.6 / 53.3).
+inline bool pick_tile(int nx, Tile& tl, int64_t n = 0) {
   if (nx < 64 || nx > 8192) return false;
   int nt = g_tune_threads;
   if (nt == 0) {
     const int per = (nx + 7) / 8;
     nt = 64;
     while (nt < per && nt < 512) nt <<= 1;
+    if ((nt == 128 && n > 256) || (nt == 256 && n > 512) || (nt == 512 && n > 0 && nx <= 4096))
+      nt >>= 1;
   }
   if (nx < nt || (nx + nt - 1) / nt > 16) return false;
   tl = tile_for(nx, nt);
@@ -149,7 +161,7 @@ inline int with_tile(const Tile& tl, F&& f) {
 }
 
 
-inline int check_model(const sch_model* md, Tile& tl) {
+inline int check_model(const sch_model* md, Tile& tl, int64_t n = 0) {
   if (!md) return fail(SCH_E_ARG, "model is NULL");
   if (!(md->L > 0) || !(md->alpha > 0) || !(md->mu >= 0) || !(md->dt > 0))
     return fail(SCH_E_ARG, "need L > 0, alpha > 0, mu >= 0, dt > 0");
@@ -158,7 +170,7 @@ inline int check_model(const sch_model* md, Tile& tl) {
   if (!md->xi) return fail(SCH_E_ARG, "xi is NULL");
   if (!(md->picard_tol > 0) || md->picard_max < 1)
     return fail(SCH_E_ARG, "need picard_tol > 0 and picard_max >= 1");
-  if (!pick_tile(md->nx, tl)) return fail(SCH_E_SHAPE, "nx = %d not supported", md->nx);
+  if (!pick_tile(md->nx, tl, n)) return fail(SCH_E_SHAPE, "nx = %d not supported", md->nx);
   return SCH_OK;
 }
 
