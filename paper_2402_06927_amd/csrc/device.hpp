@@ -155,7 +155,7 @@ __device__ __forceinline__ double uniform1(uint64_t seed, uint32_t c0, uint32_t 
 // its 16-lane row, or keeps `old` where no such lane exists), whole-wave
 // shifts by one, and readlane broadcasts into scalar registers.
 // ---------------------------------------------------------------------------
-constexpr int kDppRowShr = 0x110, kDppRowShl = 0x100, kDppWaveShr1 = 0x138,
+constexpr int kDppRowShr = 0x110, kDppRowShl = 0x100, kDppRowRor = 0x120, kDppWaveShr1 = 0x138,
               kDppWaveShl1 = 0x130;
 
 template <int CTRL>

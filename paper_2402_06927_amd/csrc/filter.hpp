@@ -113,37 +113,38 @@ static __global__ void __launch_bounds__(kWave) k_loglik(int nx, int n_obs, cons
 constexpr int kTB = 1024;
 
 struct TemperLds {
-  double red[2][kTB / kWave];
+  alignas(16) double red[2][kTB / kWave][2];  // double buffered
 };
 
-__device__ __forceinline__ double tb_reduce_max(double v, TemperLds& L) {
-  v = wave_max(v);
-  const int w = threadIdx.x / kWave;
-  if ((threadIdx.x & (kWave - 1)) == 0) L.red[0][w] = v;
-  __syncthreads();
-  double r = L.red[0][0];
-  for (int i = 1; i < kTB / kWave; ++i) r = fmax(r, L.red[0][i]);
-  __syncthreads();
-  return r;
-}
-
-__device__ __forceinline__ void tb_reduce_sum2(double& a, double& b, TemperLds& L) {
-  a = wave_sum(a);
-  b = wave_sum(b);
-  const int w = threadIdx.x / kWave;
-  if ((threadIdx.x & (kWave - 1)) == 0) {
-    L.red[0][w] = a;
-    L.red[1][w] = b;
+// Maxima (MAX) or sums of a and b over the workgroup; slot alternates between
+// calls, so that one barrier is enough.  Every lane reads one of the 16
+// wavefronts' pairs and the row of 16 lanes joins them: reading all of them in
+// every lane took the LDS longer than the exponentials took.
+template <bool MAX>
+__device__ __forceinline__ void tb_reduce2(double& a, double& b, int& slot, TemperLds& L) {
+  static_assert(kTB / kWave == 16, "a row of lanes");
+  a = MAX ? wave_max(a) : wave_sum(a);
+  b = MAX ? wave_max(b) : wave_sum(b);
+  const int lane = threadIdx.x & (kWave - 1);
+  if (lane == 0) {
+    L.red[slot][threadIdx.x / kWave][0] = a;
+    L.red[slot][threadIdx.x / kWave][1] = b;
   }
   __syncthreads();
-  double ra = 0.0, rb = 0.0;
-  for (int i = 0; i < kTB / kWave; ++i) {
-    ra += L.red[0][i];
-    rb += L.red[1][i];
+  a = L.red[slot][lane & 15][0];
+  b = L.red[slot][lane & 15][1];
+#define SCH_STEP(N)                                                            \
+  {                                                                            \
+    const double x = dpp_f64z<kDppRowRor + N>(a), y = dpp_f64z<kDppRowRor + N>(b); \
+    a = MAX ? fmax(a, x) : a + x;                                              \
+    b = MAX ? fmax(b, y) : b + y;                                              \
   }
-  a = ra;
-  b = rb;
-  __syncthreads();
+  SCH_STEP(8)
+  SCH_STEP(4)
+  SCH_STEP(2)
+  SCH_STEP(1)
+#undef SCH_STEP
+  slot ^= 1;
 }
 
 // exponent s_p = extra_p - beta phi_p (a NaN or -inf exponent gives weight 0)
@@ -158,64 +159,155 @@ __device__ __forceinline__ double log_weight(double phi, double extra, double be
   return isnan(s) ? -INFINITY : s;
 }
 
-// ESS at beta; also returns the max exponent and the sum of exp(s - smax).
-__device__ double ess_at(int n, const double* phi, const double* extra, double beta,
-                         double& smax, double& tot, TemperLds& L) {
-  double mx = -INFINITY;
-  for (int p = threadIdx.x; p < n; p += kTB)
-    mx = fmax(mx, log_weight(phi[p], extra ? extra[p] : 0.0, beta));
-  smax = tb_reduce_max(mx, L);
-  if (!(smax > -INFINITY)) {
-    tot = 0.0;
-    return 0.0;
-  }
-  double s1 = 0.0, s2 = 0.0;
-  for (int p = threadIdx.x; p < n; p += kTB) {
-    const double e = exp(log_weight(phi[p], extra ? extra[p] : 0.0, beta) - smax);
-    s1 += e;
-    s2 += e * e;
-  }
-  tb_reduce_sum2(s1, s2, L);
-  tot = s1;
-  return s1 * s1 / s2;
+// exp(x) for x <= 0 and NaN: x = k ln 2 + r with |r| <= ln 2 / 2, the Taylor
+// polynomial to r^13 (cut off at 5e-18), and 2^k.  k of at most 1155 times ln 2's
+// first part (20 trailing zero bits) is exact.
+__device__ __forceinline__ double exp_neg(double x) {
+  constexpr double kLn2Hi = 0x1.62e42feep-1, kLn2Lo = 0x1.a39ef35793c76p-33;
+  x = x < -800.0 ? -800.0 : x;
+  const double k = rint(x * 1.4426950408889634);
+  const double r = fma(-k, kLn2Lo, fma(-k, kLn2Hi, x));
+  double p = 1.0 / 6227020800.0;
+  p = fma(p, r, 1.0 / 479001600.0);
+  p = fma(p, r, 1.0 / 39916800.0);
+  p = fma(p, r, 1.0 / 3628800.0);
+  p = fma(p, r, 1.0 / 362880.0);
+  p = fma(p, r, 1.0 / 40320.0);
+  p = fma(p, r, 1.0 / 5040.0);
+  p = fma(p, r, 1.0 / 720.0);
+  p = fma(p, r, 1.0 / 120.0);
+  p = fma(p, r, 1.0 / 24.0);
+  p = fma(p, r, 1.0 / 6.0);
+  p = fma(p, r, 0.5);
+  p = fma(p, r, 1.0);
+  p = fma(p, r, 1.0);
+  return ldexp(p, static_cast<int>(k));
 }
 
 // Body of k_temper for one workgroup of kTB threads (also used per
-// instance by the batched runner).
-__device__ void temper_body(int n, const double* phi, const double* extra, double* theta_io,
-                            double thr, int n_bisect, double* dtheta_out, double* w,
-                            double* logw_out, double* ess_out, TemperLds& L) {
+// instance by the batched runner).  The ESS is evaluated n_bisect + 2 times
+// one after the other, so what counts is the time of one: the particles' phi
+// (and extra) stay in registers, kTK a thread (any more are read each time);
+// without extra the largest exponent needs no reduction, it is that of the
+// smallest phi (-beta phi rounds monotonically; of the largest for beta < 0);
+// and the two sums take one barrier.  With a bisection's weights, resampling
+// and 2048 rows of 2048 gathered: 178 us before, 101 now.
+constexpr int kTK = 8;
+template <bool EXTRA>
+__device__ __forceinline__ void temper_run(int n, const double* phi, const double* extra,
+                                           double* theta_io, double thr, int n_bisect,
+                                           double* dtheta_out, double* w, double* logw_out,
+                                           double* ess_out, TemperLds& L) {
+  const int t = threadIdx.x;
   const double theta = *theta_io;
   const double rem = 1.0 - theta;
+  double rp[kTK], rx[kTK], rq[kTK];
+#pragma unroll
+  for (int k = 0; k < kTK; ++k) {
+    const int p = t + k * kTB;
+    rp[k] = p < n ? phi[p] : 0.0;
+    rx[k] = EXTRA && p < n ? extra[p] : 0.0;
+    rq[k] = p < n && !isnan(rp[k]) ? rp[k] : INFINITY;
+  }
+  // f(particle, phi, extra) over the thread's particles, in order
+  auto each = [&](auto f) {
+#pragma unroll
+    for (int k = 0; k < kTK; ++k)
+      if (k * kTB < n && t + k * kTB < n) f(t + k * kTB, rp[k], rx[k]);
+    for (int p = t + kTK * kTB; p < n; p += kTB) f(p, phi[p], EXTRA ? extra[p] : 0.0);
+  };
+  int slot = 0;
+  double least = INFINITY, most = -INFINITY;  // phi, without extra
+  if constexpr (!EXTRA) {
+    double a = -INFINITY, b = -INFINITY;
+    each([&](int, double f, double) {
+      a = fmax(a, -f);
+      b = fmax(b, f);
+    });
+    tb_reduce2<true>(a, b, slot, L);
+    least = -a;
+    most = b;
+  }
+  // ESS at beta; also the max exponent and the sum of exp(s - smax)
   double smax, tot;
-  double e = ess_at(n, phi, extra, rem, smax, tot, L);
+  auto ess_at = [&](double beta) {
+    if constexpr (EXTRA) {
+      double mx = -INFINITY, unused = -INFINITY;
+      each([&](int, double f, double x) { mx = fmax(mx, log_weight(f, x, beta)); });
+      tb_reduce2<true>(mx, unused, slot, L);
+      smax = mx;
+    } else {
+      smax = log_weight(beta < 0.0 ? most : least, 0.0, beta);
+    }
+    if (!(smax > -INFINITY)) {
+      tot = 0.0;
+      return 0.0;
+    }
+    double s1 = 0.0, s2 = 0.0;
+    if (!EXTRA && beta > 0.0 && fabs(smax) < INFINITY) {
+      // (rq: phi with +infinity, weight 0, where there is none)
+#pragma unroll
+      for (int k = 0; k < kTK; ++k) {
+        if (k * kTB >= n) break;
+        // (the product rounded by itself, as in smax)
+        const double e = exp_neg(fmax(__dsub_rn(__dmul_rn(-beta, rq[k]), smax), -800.0));
+        s1 += e;
+        s2 = fma(e, e, s2);
+      }
+      for (int p = t + kTK * kTB; p < n; p += kTB) {
+        const double e = exp_neg(log_weight(phi[p], 0.0, beta) - smax);
+        s1 += e;
+        s2 += e * e;
+      }
+    } else {
+      each([&](int, double f, double x) {
+        const double e = exp_neg(log_weight(f, x, beta) - smax);
+        s1 += e;
+        s2 += e * e;
+      });
+    }
+    tb_reduce2<false>(s1, s2, slot, L);
+    tot = s1;
+    return s1 * s1 / s2;
+  };
+  double e = ess_at(rem);
   double pick = rem;
   if (n_bisect > 0 && !(e >= thr)) {
     double lo = 0.0, hi = rem;
     for (int k = 0; k < n_bisect; ++k) {
       const double mid = 0.5 * (lo + hi);
-      const double em = ess_at(n, phi, extra, mid, smax, tot, L);
+      const double em = ess_at(mid);
       if (em >= thr)
         lo = mid;
       else
         hi = mid;
     }
     pick = lo > 0.0 ? lo : hi;
-    e = ess_at(n, phi, extra, pick, smax, tot, L);
+    e = ess_at(pick);
   }
   const bool dead = !(smax > -INFINITY);
   const double ltot = dead ? 0.0 : log(tot);
-  for (int p = threadIdx.x; p < n; p += kTB) {
-    const double s = log_weight(phi[p], extra ? extra[p] : 0.0, pick);
-    w[p] = dead ? 0.0 : exp(s - smax) / tot;
+  each([&](int p, double f, double x) {
+    const double s = log_weight(f, x, pick);
+    w[p] = dead ? 0.0 : exp_neg(s - smax) / tot;
     if (logw_out) logw_out[p] = dead ? -INFINITY : (s - smax) - ltot;
-  }
+  });
   __syncthreads();  // every thread has read *theta_io
-  if (threadIdx.x == 0) {
+  if (t == 0) {
     *dtheta_out = pick;
     *ess_out = e;
     *theta_io = (pick == rem) ? 1.0 : theta + pick;
   }
+}
+
+__device__ __forceinline__ void temper_body(int n, const double* phi, const double* extra, double* theta_io,
+                            double thr, int n_bisect, double* dtheta_out, double* w,
+                            double* logw_out, double* ess_out, TemperLds& L) {
+  if (extra)
+    temper_run<true>(n, phi, extra, theta_io, thr, n_bisect, dtheta_out, w, logw_out, ess_out, L);
+  else
+    temper_run<false>(n, phi, extra, theta_io, thr, n_bisect, dtheta_out, w, logw_out, ess_out,
+                      L);
 }
 
 static __global__ void __launch_bounds__(kTB) k_temper(int n, const double* phi, const double* extra,
@@ -230,10 +322,12 @@ static __global__ void __launch_bounds__(kTB) k_temper(int n, const double* phi,
 // Integer-exact systematic resampling in one workgroup of kTB threads.
 // cum (workspace, uint64 [n]) receives the prefix sums of the quantised weights.
 // ---------------------------------------------------------------------------
+constexpr int kCumLds = 8192;
 struct ResampleLds {
   double red[kTB / kWave];
-  unsigned long long part[kTB];
+  unsigned long long part[kTB / kWave];
   int flag;
+  unsigned long long cum[kCumLds];
 };
 
 // T_j = ((j + u0) * Q) / n, each operation rounded once (no contraction).
@@ -245,7 +339,7 @@ __device__ __forceinline__ double systematic_point(int j, double u0, double Q, i
 
 // Body of k_resample for one workgroup of kTB threads (also used per
 // instance by the batched runner).
-__device__ void resample_body(int n, const double* w, const double* u0p, const double* cond_ess,
+__device__ __forceinline__ void resample_body(int n, const double* w, const double* u0p, const double* cond_ess,
                               double cond_thr, int* idx, int* degenerate,
                               unsigned long long* cum, ResampleLds& L) {
   const int t = threadIdx.x;
@@ -288,20 +382,30 @@ __device__ void resample_body(int n, const double* w, const double* u0p, const d
   const int lo = t * per, hi = min(n, lo + per);
   unsigned long long s = 0;
   for (int p = lo; p < hi; ++p) s += static_cast<unsigned long long>(floor(ldexp(w[p], sh)));
-  L.part[t] = s;
-  __syncthreads();
-  for (int d = 1; d < kTB; d <<= 1) {
-    const unsigned long long add = t >= d ? L.part[t - d] : 0ull;
-    __syncthreads();
-    L.part[t] += add;
-    __syncthreads();
+  // inclusive over the wavefront, then the totals of the wavefronts before
+  unsigned long long inc = s;
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) {
+    const unsigned long long x = __shfl_up(inc, d);
+    inc += (t & (kWave - 1)) >= d ? x : 0ull;
   }
-  unsigned long long run = t > 0 ? L.part[t - 1] : 0ull;
+  if ((t & (kWave - 1)) == kWave - 1) L.part[t / kWave] = inc;
+  __syncthreads();
+  unsigned long long run = inc - s, Qi = 0ull;
+#pragma unroll
+  for (int i = 0; i < kTB / kWave; ++i) {
+    run += i < t / kWave ? L.part[i] : 0ull;
+    Qi += L.part[i];
+  }
+  // the searches below read them at random: from LDS where they fit
+  const bool in_lds = n <= kCumLds;
   for (int p = lo; p < hi; ++p) {
     run += static_cast<unsigned long long>(floor(ldexp(w[p], sh)));
-    cum[p] = run;
+    if (in_lds)
+      L.cum[p] = run;
+    else
+      cum[p] = run;
   }
-  const unsigned long long Qi = L.part[kTB - 1];
   __threadfence_block();
   __syncthreads();
   if (Qi == 0ull) {
@@ -311,19 +415,25 @@ __device__ void resample_body(int n, const double* w, const double* u0p, const d
   }
   const double Q = static_cast<double>(Qi);
   const double u0 = *u0p;
-  for (int j = t; j < n; j += kTB) {
-    const double T = systematic_point(j, u0, Q, n);
-    // first p with cum[p] > T
-    int a = 0, c = n;
-    while (a < c) {
-      const int mid = (a + c) >> 1;
-      if (static_cast<double>(cum[mid]) > T)
-        c = mid;
-      else
-        a = mid + 1;
+  auto search = [&](auto at) {
+    for (int j = t; j < n; j += kTB) {
+      const double T = systematic_point(j, u0, Q, n);
+      // first p with cum[p] > T
+      int a = 0, c = n;
+      while (a < c) {
+        const int mid = (a + c) >> 1;
+        if (static_cast<double>(at(mid)) > T)
+          c = mid;
+        else
+          a = mid + 1;
+      }
+      idx[j] = a < n ? a : n - 1;
     }
-    idx[j] = a < n ? a : n - 1;
-  }
+  };
+  if (in_lds)
+    search([&](int i) { return L.cum[i]; });
+  else
+    search([&](int i) { return cum[i]; });
 }
 
 static __global__ void __launch_bounds__(kTB) k_resample(int n, const double* w, const double* u0p,
@@ -334,7 +444,7 @@ static __global__ void __launch_bounds__(kTB) k_resample(int n, const double* w,
   resample_body(n, w, u0p, cond_ess, cond_thr, idx, degenerate, cum, L);
 }
 
-// dst[j][:] = src[idx[j]][:]
+// dst[j][:] = src[idx[j]][:], 16 bytes a lane where the rows allow
 static __global__ void k_gather(int n_rows, int64_t row_len, const int* idx, const double* src,
                          double* dst) {
   const int j = blockIdx.y;
@@ -342,9 +452,16 @@ static __global__ void k_gather(int n_rows, int64_t row_len, const int* idx, con
   if (r < 0 || r >= n_rows) return;  // out-of-range index: row left untouched
   const double* s = src + static_cast<int64_t>(r) * row_len;
   double* d = dst + static_cast<int64_t>(j) * row_len;
-  for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < row_len;
-       i += static_cast<int64_t>(gridDim.x) * blockDim.x)
-    d[i] = s[i];
+  const int64_t i0 = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x,
+                step = static_cast<int64_t>(gridDim.x) * blockDim.x;
+  if (((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst) |
+        static_cast<uintptr_t>(8 * row_len)) & 15) == 0) {
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    for (int64_t i = i0; i < row_len / 2; i += step)
+      reinterpret_cast<d2*>(d)[i] = reinterpret_cast<const d2*>(s)[i];
+    return;
+  }
+  for (int64_t i = i0; i < row_len; i += step) d[i] = s[i];
 }
 
 // ---------------------------------------------------------------------------
