@@ -3,6 +3,8 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
+#include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -53,15 +55,69 @@ CycleWs carve_cycle(void* base, int which, int nx, int nq, int n, int ns, size_t
   w.dW = c.take<double>(inc);
   w.phi = c.take<double>(n);
   w.w = c.take<double>(n);
-  w.scal = c.take<double>(8);
   w.idx = c.take<int>(n);
-  w.status = c.take<int>(n);
   w.iters = c.take<int>(n);
   w.degenerate = c.take<int>(4);
   w.cum = c.take<unsigned long long>(n);
+  // what the host reads after a cycle, side by side (Readback)
+  w.scal = c.take<double>(8);
+  w.status = c.take<int>(n);
   w.acc = c.take<unsigned long long>(4);
   if (bytes) *bytes = c.off + 256;
   return w;
+}
+
+// The scalars, statuses and counters of a cycle in one copy (each copy to the
+// host waits for its own: about 10 us on an otherwise idle stream).
+struct Readback {
+  std::vector<unsigned char> buf;
+  double ess = 0.0;
+  unsigned long long acc[4] = {0, 0, 0, 0};
+  int n_failed = 0;
+  int read(const CycleWs& W, int n, hipStream_t st) {
+    const auto at = [&](const void* p) {
+      return static_cast<size_t>(static_cast<const char*>(p) -
+                                 reinterpret_cast<const char*>(W.scal));
+    };
+    buf.resize(at(W.acc + 4));
+    HIP_TRY(hipMemcpyAsync(buf.data(), W.scal, buf.size(), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    std::memcpy(&ess, buf.data() + at(W.scal + 2), sizeof ess);
+    std::memcpy(acc, buf.data() + at(W.acc), sizeof acc);
+    const int* status = reinterpret_cast<const int*>(buf.data() + at(W.status));
+    n_failed = 0;
+    for (int p = 0; p < n; ++p) n_failed += status[p] != SCH_OK;
+    return SCH_OK;
+  }
+};
+
+// Rows of several fields resampled in place: field[j][:] = field[idx[j]][:].
+struct GatherField {
+  double* p;
+  int64_t len;
+};
+int resample_rows(int n, std::initializer_list<GatherField> fields, const int* idx,
+                  double* scratch, hipStream_t st) {
+  if (n <= kGatherRows) {
+    GatherSet G{};
+    G.n = n;
+    for (const GatherField& f : fields) {
+      const int k = G.n_fields++;
+      G.p[k] = f.p;
+      G.len[k] = f.len;
+      G.first[k + 1] = G.first[k] + static_cast<int>((f.len + kGatherCols - 1) / kGatherCols);
+    }
+    hipLaunchKernelGGL(k_gather_rows, dim3(G.first[G.n_fields]), dim3(256),
+                       sizeof(double) * kGatherCols * static_cast<size_t>(n), st, G, idx);
+    CHECK_LAUNCH();
+    return SCH_OK;
+  }
+  for (const GatherField& f : fields) {
+    if (int rc = sch_gather(n, f.len, idx, f.p, scratch, st)) return rc;
+    HIP_TRY(hipMemcpyAsync(f.p, scratch, sizeof(double) * static_cast<size_t>(n) * f.len,
+                           hipMemcpyDeviceToDevice, st));
+  }
+  return SCH_OK;
 }
 
 // M != null: the Matern-type noise, dW holds cells [n][n_steps][nx].
@@ -504,7 +560,6 @@ int temper_loop(const sch_model& md, const Tile& tl, const sch_obs& ob, uint64_t
                 const MaternDev* M = nullptr, const PcnlWs* PW = nullptr) {
   void* stream = st;
   const int nx = md.nx, Q = M ? md.nx : md.n_modes;
-  const size_t state = static_cast<size_t>(n) * nx, inc = static_cast<size_t>(n) * n_steps * Q;
   hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, st, W.scal, 0.0, int64_t(1));  // theta = 0
   int k = 0, rc = SCH_OK;
   double theta = 0.0, ess = 0.0;
@@ -531,23 +586,13 @@ int temper_loop(const sch_model& md, const Tile& tl, const sch_obs& ob, uint64_t
     }
     {
       TimedScope ts(SCH_TK_GATHER, st);
-      double* fields[4] = {W.m0, W.u0, m, u};
-      for (double* f : fields) {
-        if (int r2 = sch_gather(n, nx, W.idx, f, W.scratch, stream)) return r2;
-        HIP_TRY(hipMemcpyAsync(f, W.scratch, sizeof(double) * state, hipMemcpyDeviceToDevice, st));
-      }
-      if (int r2 = sch_gather(n, static_cast<int64_t>(n_steps) * Q, W.idx, W.dW, W.scratch, stream))
-        return r2;
-      HIP_TRY(hipMemcpyAsync(W.dW, W.scratch, sizeof(double) * inc, hipMemcpyDeviceToDevice, st));
-      if (int r2 = sch_gather(n, 1, W.idx, W.phi, W.scratch, stream)) return r2;
-      HIP_TRY(hipMemcpyAsync(W.phi, W.scratch, sizeof(double) * n, hipMemcpyDeviceToDevice, st));
-      if (dLam) {
-        if (int r2 = sch_gather(n, static_cast<int64_t>(n_steps) * Q, W.idx, dLam, W.scratch,
-                                stream))
-          return r2;
-        HIP_TRY(hipMemcpyAsync(dLam, W.scratch, sizeof(double) * inc, hipMemcpyDeviceToDevice,
-                               st));
-      }
+      const int64_t li = static_cast<int64_t>(n_steps) * Q;
+      const GatherField f0{W.m0, nx}, f1{W.u0, nx}, f2{m, nx}, f3{u, nx}, f4{W.dW, li},
+          f5{W.phi, 1};
+      const int r2 = dLam ? resample_rows(n, {f0, f1, f2, f3, f4, f5, {dLam, li}}, W.idx,
+                                          W.scratch, st)
+                          : resample_rows(n, {f0, f1, f2, f3, f4, f5}, W.idx, W.scratch, st);
+      if (r2) return r2;
     }
     if (n_jitter > 0 && PW) {
       TimedScope ts(SCH_TK_JITTER, st);
@@ -578,9 +623,11 @@ int temper_loop(const sch_model& md, const Tile& tl, const sch_obs& ob, uint64_t
         return r2;
       psteps += static_cast<int64_t>(n) * n_steps * n_jitter;
     }
-    HIP_TRY(hipMemcpyAsync(&theta, W.scal + 0, sizeof(double), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipMemcpyAsync(&ess, W.scal + 2, sizeof(double), hipMemcpyDeviceToHost, st));
+    double scal[3];  // theta, its step, the ESS
+    HIP_TRY(hipMemcpyAsync(scal, W.scal, sizeof scal, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
+    theta = scal[0];
+    ess = scal[2];
     timing_flush();
     // the adjoint evaluations of a gradient-based stage: the Picard iterations
     // of their forward sweeps count with the stage's, the transposed ones with
@@ -595,11 +642,9 @@ int temper_loop(const sch_model& md, const Tile& tl, const sch_obs& ob, uint64_t
       break;
     }
   }
-  unsigned long long acc[3] = {0, 0, 0};
-  std::vector<int> status(n);
-  HIP_TRY(hipMemcpyAsync(acc, W.acc, sizeof acc, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(status.data(), W.status, sizeof(int) * n, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipStreamSynchronize(st));
+  Readback back;
+  if (int r2 = back.read(W, n, st)) return r2;
+  const unsigned long long* acc = back.acc;
   timing_flush();
   g_tm.iters[SCH_TK_WINDOW] += static_cast<long long>(acc[0]);
   g_tm.iters[SCH_TK_JITTER] += static_cast<long long>(acc[2]);
@@ -608,7 +653,7 @@ int temper_loop(const sch_model& md, const Tile& tl, const sch_obs& ob, uint64_t
   stats->picard_iters = static_cast<int64_t>(acc[0] + acc[2]);
   stats->n_accept = static_cast<int64_t>(acc[1]);
   stats->particle_steps = psteps;
-  for (int p = 0; p < n; ++p) stats->n_failed += status[p] != SCH_OK;
+  stats->n_failed += back.n_failed;
   stats->status = rc;
   return rc;
 }
@@ -1029,20 +1074,17 @@ int bootstrap_cycle(const sch_model* md, const Tile& tl, const sch_obs* ob, uint
                                 W.scal + 2, stream))
       return rc;
   }
-  double ess = 0.0;
-  unsigned long long its = 0;
-  HIP_TRY(hipMemcpyAsync(&ess, W.scal + 2, sizeof(double), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(&its, W.acc, sizeof its, hipMemcpyDeviceToHost, st));
-  std::vector<int> status(n);
-  HIP_TRY(hipMemcpyAsync(status.data(), W.status, sizeof(int) * n, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipStreamSynchronize(st));
+  Readback back;
+  if (int r2 = back.read(W, n, st)) return r2;
+  const double ess = back.ess;
+  const unsigned long long its = back.acc[0];
   timing_flush();
   g_tm.iters[SCH_TK_WINDOW] += static_cast<long long>(its);
   stats->ess = ess;
   stats->picard_iters = static_cast<int64_t>(its);
   stats->particle_steps = static_cast<int64_t>(n) * n_steps;
   int rc = SCH_OK;
-  for (int p = 0; p < n; ++p) stats->n_failed += status[p] != SCH_OK;
+  stats->n_failed += back.n_failed;
   if (!(ess > 0.0)) {
     stats->status = SCH_E_DEGENERATE;
     return fail(SCH_E_DEGENERATE, "all weights vanished in cycle %u", cycle);
@@ -1056,10 +1098,7 @@ int bootstrap_cycle(const sch_model* md, const Tile& tl, const sch_obs* ob, uint
         return r2;
     }
     TimedScope ts(SCH_TK_GATHER, st);
-    if (int r2 = sch_gather(n, nx, W.idx, m, W.scratch, stream)) return r2;
-    HIP_TRY(hipMemcpyAsync(m, W.scratch, sizeof(double) * n * nx, hipMemcpyDeviceToDevice, st));
-    if (int r2 = sch_gather(n, nx, W.idx, u, W.scratch, stream)) return r2;
-    HIP_TRY(hipMemcpyAsync(u, W.scratch, sizeof(double) * n * nx, hipMemcpyDeviceToDevice, st));
+    if (int r2 = resample_rows(n, {{m, nx}, {u, nx}}, W.idx, W.scratch, st)) return r2;
     hipLaunchKernelGGL(k_fill, dim3(grid_for(n, 256)), dim3(256), 0, st, logw, 0.0, int64_t(n));
     CHECK_LAUNCH();
     stats->resampled = 1;

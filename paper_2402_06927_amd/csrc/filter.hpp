@@ -464,6 +464,39 @@ static __global__ void k_gather(int n_rows, int64_t row_len, const int* idx, con
   for (int64_t i = i0; i < row_len; i += step) d[i] = s[i];
 }
 
+// Rows of up to eight fields resampled in place, one launch where a gather and
+// a copy back of each took two: a workgroup owns kGatherCols columns (a cache
+// line of a row) of a field, reads all their rows into LDS and then writes
+// them.  Up to kGatherRows rows fit (64 KB).  Rows that stay are left alone, as
+// are those of an index out of range.
+constexpr int kGatherRows = 512, kGatherCols = 16;
+struct GatherSet {
+  int n, n_fields, first[9];  // first block of each field
+  double* p[8];
+  int64_t len[8];
+};
+static __global__ void __launch_bounds__(256) k_gather_rows(const GatherSet G, const int* idx) {
+  extern __shared__ double rows[];
+  int f = 0;
+  while (f + 1 < G.n_fields && static_cast<int>(blockIdx.x) >= G.first[f + 1]) ++f;
+  double* p = G.p[f];
+  const int64_t len = G.len[f];
+  const int c = threadIdx.x % kGatherCols;
+  const int64_t col = static_cast<int64_t>(blockIdx.x - G.first[f]) * kGatherCols + c;
+  const bool in = col < len;
+#pragma unroll 4
+  for (int j = threadIdx.x / kGatherCols; j < G.n; j += 256 / kGatherCols) {
+    const int r = idx[j];
+    if (in && r != j && r >= 0 && r < G.n) rows[j * kGatherCols + c] = p[r * len + col];
+  }
+  __syncthreads();
+#pragma unroll 4
+  for (int j = threadIdx.x / kGatherCols; j < G.n; j += 256 / kGatherCols) {
+    const int r = idx[j];
+    if (in && r != j && r >= 0 && r < G.n) p[j * len + col] = rows[j * kGatherCols + c];
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Ensemble statistics of section 4 (EMRE, RB, RES) against a truth row.
 // ---------------------------------------------------------------------------

@@ -116,3 +116,23 @@ def test_default_tile_by_ensemble(sch, nx, n, threads):
     finally:
         sch.sch_tune_set(sch.TUNE_THREADS, 0)
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("nx,n", [(65, 17), (100, 512), (100, 513)])
+def test_rows_resampled_in_a_cycle(sch, nx, n):
+    """The state's rows after a resampling, on both sides of the ensemble size
+    up to which they change places in LDS."""
+    wl = W.BOOTSTRAP_256.scaled(nx=nx, n_modes=3, n_steps=2, n_obs=40, n_particles=n)
+    om, gm = PR.oracle_model(wl), PR.gpu_model(wl)
+    u0, m0, _, _ = PR.prior(wl, n)
+    y, sig = PR.oracle_observations(wl, 1)[0], np.full(wl.n_obs, wl.sigma_obs)
+    rc, m_o, u_o, _, st_o = O.bootstrap_cycle(om, y, sig, wl.seed, 0, m0, u0, np.zeros(n),
+                                              wl.n_steps, 1.01)
+    assert rc == 0 and st_o.resampled
+    m, u, lw = _dev(m0), _dev(u0), _dev(np.zeros(n))
+    st = sch.sch_pf_bootstrap_cycle(gm, sch.Obs(_dev(y), _dev(sig)), wl.seed, 0, m, u, lw,
+                                    wl.n_steps, 1.01,
+                                    sch.workspace(sch.WS_BOOTSTRAP, gm, n, wl.n_steps))
+    assert st["resampled"] == 1 and abs(st["ess"] - st_o.ess) < 1e-9 * st_o.ess
+    assert PR.rel_l2(m.cpu().numpy(), m_o) < PR.REL_TOL
+    assert PR.rel_l2(u.cpu().numpy(), u_o) < PR.REL_TOL
