@@ -818,7 +818,8 @@ int sch_mlp_controls(int32_t n, int32_t cols, const float *Y, const float *mean,
 /* --------------------------------------------------------------------------
  * Tuning knobs (process-global).  SCH_TUNE_THREADS forces the threads per
  * particle of the model kernels (a power of two in 64..512; 0 = automatic:
- * the smallest power of two giving at most 8 nodes per thread).  A value
+ * the smallest power of two giving at most 8 nodes per thread, or half of it
+ * where the call's ensemble fills the chip).  A value
  * that leaves more than 16 nodes per thread, or fewer than one, makes the
  * model calls return SCH_E_SHAPE.  sch_tune_get returns the current value
  * (-1 for an unknown key).
