@@ -275,7 +275,7 @@ struct RowLds {
   alignas(16) double eq[4][NT > kWave ? NT : 2];
   double etail[3][W];          // last-row spike values of each wavefront's last chunk
   double edge[2][W][6];        // wavefront edge values of halo exchanges, double buffered
-  double red[3][W];            // workgroup reductions
+  double red[W];               // workgroup sums
   // per-wavefront records of solve_helm(), double buffered: the scans' totals,
   // the factor of the wavefront's rows (ragged grids), and the reduction that
   // rides along
@@ -826,40 +826,14 @@ __device__ __forceinline__ void cyclic_solve(RowF row, DF d, double (&x)[PMAX], 
   cyclic_solve<PMAX, NT, FULL>(row, d, x, cnt, L, t, xl, xr, grow);
 }
 
-// Workgroup-wide max of two values and bitwise or of small nonnegative flags.
-template <int NT>
-__device__ __forceinline__ void block_max2_or(double& a, double& b, int& f, RowLds<NT>& L, int t) {
-  a = wave_max(a);
-  b = wave_max(b);
-  f = wave_or(f);
-  const int w = t / kWave;
-  if ((t & (kWave - 1)) == 0) {
-    L.red[0][w] = a;
-    L.red[1][w] = b;
-    L.red[2][w] = static_cast<double>(f);
-  }
-  __syncthreads();
-  a = L.red[0][0];
-  b = L.red[1][0];
-  int ff = static_cast<int>(L.red[2][0]);
-#pragma unroll
-  for (int i = 1; i < NT / kWave; ++i) {
-    a = fmax(a, L.red[0][i]);
-    b = fmax(b, L.red[1][i]);
-    ff |= static_cast<int>(L.red[2][i]);
-  }
-  f = ff;
-  __syncthreads();
-}
-
 template <int NT>
 __device__ __forceinline__ double block_sum(double a, RowLds<NT>& L, int t) {
   a = wave_sum(a);
-  if ((t & (kWave - 1)) == 0) L.red[0][t / kWave] = a;
+  if ((t & (kWave - 1)) == 0) L.red[t / kWave] = a;
   __syncthreads();
   double s = 0.0;
 #pragma unroll
-  for (int i = 0; i < NT / kWave; ++i) s += L.red[0][i];
+  for (int i = 0; i < NT / kWave; ++i) s += L.red[i];
   __syncthreads();
   return s;
 }

@@ -47,15 +47,6 @@ __device__ __forceinline__ void mass_apply_h(const double (&v)[PMAX], double (&o
     out[j] = fma(c1, left_of<PMAX, FULL>(v, j, hl) + right_of<PMAX, FULL>(v, j, cnt, hr), c0 * v[j]);
 }
 
-// The same with the halo exchanged through LDS.
-template <int PMAX, int NT, bool FULL>
-__device__ __forceinline__ void mass_apply(const double (&v)[PMAX], double (&out)[PMAX], double h,
-                                           int cnt, RowLds<NT>& L, int t, double scale, int& hs) {
-  double hl, hr;
-  halo<PMAX, NT, FULL>(v, cnt, L, t, hl, hr, hs);
-  mass_apply_h<PMAX, FULL>(v, out, h, cnt, hl, hr, scale);
-}
-
 // Per-thread solver state carried through a kernel: the halo and record
 // buffer parities.
 struct Parity {
