@@ -159,6 +159,17 @@ __device__ __forceinline__ double log_weight(double phi, double extra, double be
   return isnan(s) ? -INFINITY : s;
 }
 
+// -beta phi - smax with the product rounded by itself, as it is in smax and in
+// the weights: fused, the exponents would keep the product's remainder (up to
+// 7e-9 at phi = 1e8) that the others have dropped, and the weights would not
+// add up to 1.  (__dmul_rn and __dsub_rn are plain operators in HIP, which the
+// compiler contracts.)
+__device__ __forceinline__ double exponent_below(double beta, double phi, double smax) {
+#pragma clang fp contract(off)
+  const double s = -beta * phi;
+  return s - smax;
+}
+
 // exp(x) for x <= 0 and NaN: x = k ln 2 + r with |r| <= ln 2 / 2, the Taylor
 // polynomial to r^13 (cut off at 5e-18), and 2^k.  k of at most 1155 times ln 2's
 // first part (20 trailing zero bits) is exact.
@@ -249,8 +260,7 @@ __device__ __forceinline__ void temper_run(int n, const double* phi, const doubl
 #pragma unroll
       for (int k = 0; k < kTK; ++k) {
         if (k * kTB >= n) break;
-        // (the product rounded by itself, as in smax)
-        const double e = exp_neg(fmax(__dsub_rn(__dmul_rn(-beta, rq[k]), smax), -800.0));
+        const double e = exp_neg(fmax(exponent_below(beta, rq[k], smax), -800.0));
         s1 += e;
         s2 = fma(e, e, s2);
       }

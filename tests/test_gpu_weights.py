@@ -6,6 +6,8 @@ cannot take, and the tile that the number of particles picks.
 Weights against the oracle at relative L2 1e-12 (each side errs by a few ulp in
 the exponential and n eps in the sum), bisected steps at the parity test's
 bars; indices and rows exactly."""
+import math
+
 import numpy as np
 import pytest
 
@@ -64,6 +66,23 @@ def test_weights(sch, n, bad):
         d_ref, w_ref, e_ref = O.temper(phi, 0.0, 0.5 * n, 50)
         assert abs(dth - d_ref) <= 1e-12 * d_ref + 2.0 ** -40
         assert abs(ess - e_ref) < 1e-9 * e_ref and PR.rel_l2(w, w_ref) < 1e-9
+
+
+@pytest.mark.parametrize("offset", [1e5, 1e8])
+@pytest.mark.parametrize("n", [5, 1024, 8193])
+def test_weights_of_potentials_far_from_zero(sch, n, offset):
+    """A common offset drops out of the weights: beta phi is rounded once, alike
+    for the largest exponent, the sum and the weights (an ulp of beta phi is
+    7e-12 at 1e5 and 7e-9 at 1e8).  Both sides then exponentiate the same
+    differences, so test_weights' bar holds; the weights add up to 1."""
+    phi = offset + _phi(n, False)
+    for x in (None, np.zeros(n)):
+        for beta in (1.0, 0.75):
+            _, _, ess, w, _ = _temper(sch, phi, 1.0 - beta, 0.0, 0, x)
+            e_ref, w_ref, _ = O.weights(phi, beta, x)
+            assert abs(ess - e_ref) <= 1e-12 * e_ref, (beta, ess, e_ref)
+            assert PR.rel_l2(w, w_ref) < 1e-12, beta
+            assert abs(math.fsum(w) - 1.0) < 1e-12, beta
 
 
 def test_no_particle_left(sch):
