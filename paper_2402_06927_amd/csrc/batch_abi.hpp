@@ -5,7 +5,9 @@
 #pragma once
 
 #include <algorithm>
+#include <map>
 #include <numeric>
+#include <utility>
 #include <vector>
 
 #include "adjoint.hpp"
@@ -36,11 +38,12 @@ using namespace sch;
 constexpr size_t kMaxClasses = 32;  // four thread counts, five slot counts
 
 // Tile of one instance: the threads the caller asked for, else the model
-// calls' choice for the G particles of all instances; nodes per thread 4, 6, 8, 12 or 16 (the batched kernels take
-// ragged chunks, so a 2-slot choice runs on 4 slots).
-bool batch_tile(const sch_instance& in, Tile& tl, int64_t G) {
+// calls' choice for n particles (batch_tiles; n = 0: the tile for short
+// chunks); nodes per thread 4, 6, 8, 12 or 16 (the batched kernels take ragged
+// chunks, so a 2-slot choice runs on 4 slots).
+bool batch_tile(const sch_instance& in, Tile& tl, int64_t n) {
   if (in.threads == 0) {
-    if (!pick_tile(in.nx, tl, G)) return false;
+    if (!pick_tile(in.nx, tl, n)) return false;
   } else {
     const int nt = in.threads;
     if (nt < 64 || nt > 512 || (nt & (nt - 1)) != 0 || in.nx < nt || (in.nx + nt - 1) / nt > 16)
@@ -52,6 +55,22 @@ bool batch_tile(const sch_instance& in, Tile& tl, int64_t G) {
     tl.full = false;
   }
   return tile_rows_ok(in.nx, tl);
+}
+
+// Tiles of all instances.  The tile classes are launched one after another, so
+// the particles that wait for each other are those of one launch: the choice
+// goes by the particles of the instances that short chunks would put into the
+// same class.
+std::vector<Tile> batch_tiles(int n_inst, const sch_instance* in) {
+  std::vector<Tile> tiles(n_inst);
+  std::map<std::pair<int, int>, int64_t> n;
+  for (int i = 0; i < n_inst; ++i) {
+    batch_tile(in[i], tiles[i], 0);
+    n[{tiles[i].nt, tiles[i].pmax}] += in[i].n_particles;
+  }
+  for (int i = 0; i < n_inst; ++i)
+    batch_tile(in[i], tiles[i], n[{tiles[i].nt, tiles[i].pmax}]);
+  return tiles;
 }
 
 struct Layout {
@@ -105,7 +124,7 @@ int check_batch(const sch_batch_params* bp, int n_inst, const sch_instance* in, 
     if (s.nx < 64 || s.nx > 8192 || s.n_particles < 1 || s.n_particles > 65536)
       return fail(SCH_E_SHAPE, "instance %d: nx = %d, n = %d not supported", i, s.nx,
                   s.n_particles);
-    if (!batch_tile(s, tl, 1))
+    if (!batch_tile(s, tl, 0))
       return fail(SCH_E_SHAPE, "instance %d: no tile for nx = %d with %d threads", i, s.nx,
                   s.threads);
     G += s.n_particles;
@@ -201,11 +220,10 @@ int sch_batch_create(const sch_batch_params* bp, int32_t n_inst, const sch_insta
   // per-instance table and the particle -> instance map
   std::vector<InstDev> inst(n_inst);
   std::vector<int> pinst(G);
-  std::vector<Tile> tiles(n_inst);
+  const std::vector<Tile> tiles = batch_tiles(n_inst, in);
   int64_t g0 = 0, s0 = 0;
   for (int i = 0; i < n_inst; ++i) {
     const sch_instance& s = in[i];
-    batch_tile(s, tiles[i], G);
     sch_model md{bp->L, bp->alpha, bp->mu, bp->dt, s.nx, bp->n_modes, s.xi, bp->picard_tol,
                  bp->picard_max};
     InstDev& D = inst[i];

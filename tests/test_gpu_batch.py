@@ -140,6 +140,28 @@ def test_batch_graph_replays_match_direct_launches(sch):
     assert runs[0][2]["picard_iters"] == runs[1][2]["picard_iters"]
 
 
+@pytest.mark.parametrize("sizes,threads", [
+    (((2048, 24), (256, 600)), (256, 64)),              # the companions run in another launch
+    (((1500, 300), (1400, 300)), (128, 128)),           # together too many for short chunks
+    (((1500, 256), (1400, 256), (2000, 30)), (256, 256, 256)),
+    (((600, 130), (700, 130), (1000, 30), (3000, 3)), (64, 64, 128, 256)),
+])
+def test_batch_default_tile_counts_its_launch(sch, sizes, threads):
+    """An instance's default tile goes by the particles that share its launch,
+    not by those of the whole batch: the bits are those of the tile asked for by
+    name."""
+    base = W.BOOTSTRAP_256.scaled(n_steps=1, n_modes=2)
+    insts = [W.Instance(nx, n, 11 + 2 * k) for k, (nx, n) in enumerate(sizes)]
+    runs = []
+    for t in (None, threads):
+        b, gi, _ = _setup(sch, base, insts, 1, threads=t, checked=set())
+        b.run(0, 1, use_graph=False)
+        runs.append([(N(g.m), N(g.u)) for g in gi])
+        b.close()
+    for k, (a, c) in enumerate(zip(*runs)):
+        assert np.array_equal(a[0], c[0]) and np.array_equal(a[1], c[1]), sizes[k]
+
+
 def test_batch_rejects_bad_instances(sch):
     """Shape and argument errors are reported before any device work."""
     base = W.BOOTSTRAP_256.scaled(n_steps=2)
