@@ -461,6 +461,21 @@ __device__ __forceinline__ int sweeps_for(double a, double c) {
   return __any(!(e <= kSweep6)) ? 0 : 6;
 }
 
+// Whether a pivot is 16 times smaller than a coupling of its equation, or more
+// (where the rows are diagonally dominant none is smaller at all): eliminating
+// with it would drown the neighbours.  On the high words of what is there
+// before the reciprocal: compared in FP64, or taken from the quotients, it cost
+// the adjoint and the forecast 2%.
+__device__ __forceinline__ bool drowns(double pivot, double a, double c) {
+  const auto word = [](double v) {
+    return static_cast<uint32_t>(__double2hiint(v)) & 0x7fffffffu;
+  };
+  return max(word(a), word(c)) >= word(pivot) + 0x400000u;
+}
+__device__ __forceinline__ double nan_if(bool bad, double v) {
+  return bad ? __hiloint2double(0x7ff80000, __double2loint(v)) : v;
+}
+
 // The same system over the 64 lanes of one wavefront, lane l holding equation
 // l (periodic): sweeps where they suffice, cyclic reduction levels (which
 // square the couplings and double the distance d of the coupled lanes) until
@@ -612,9 +627,9 @@ __device__ __forceinline__ void interface_solve(const double (&eA)[NT / kWave],
 // the solution's error grows about like max |c'| times the unit roundoff
 // (near-zero pivots of a compressive saw-tooth dv: max |c'| = 250 gives a
 // relative error of 1e-14, 2.5e5 gives 6e-13, 2.5e8 gives 6e-10).  `grow`
-// receives the running maximum of |c'_j| over the chunk's rows and the
-// interface elimination, and callers reject a system whose growth exceeds
-// kMaxGrowth = 2^16 (errors below about 1e-12).
+// receives the running maximum of |c'_j| over the chunk's rows and
+// interface_solve()'s eliminations, and callers reject a system whose growth
+// exceeds kMaxGrowth = 2^16 (errors below about 1e-12).
 constexpr double kMaxGrowth = 65536.0;
 #ifndef SCH_SWEEP_FENCE
 #define SCH_SWEEP_FENCE 4
@@ -738,8 +753,15 @@ __device__ __forceinline__ void cyclic_solve(RowF row, DF d, double (&x)[PMAX], 
         kpl = tk;
       }
     }
-    const double i1 = rcp64(eB.y), y = eR.y * i1, g1 = -eA.y * i1, k1 = -eC.y * i1;
-    grow = vmax_abs(grow, k1);
+    //
+    // This eliminates in another order than interface_solve(), which measures
+    // its growth; its own is bounded instead: a pivot that drowns() the
+    // neighbours makes them not a number, which sweeps_for() refuses, and the
+    // system is left to interface_solve().  (Even couplings of 3e5 cost 1e-8 of
+    // the solution where that one errs by 1e-13, and it may not meet at all an
+    // odd pivot that would have to be refused here.)
+    const double i1 = nan_if(drowns(eB.y, eA.y, eC.y), rcp64(eB.y));
+    const double y = eR.y * i1, g1 = -eA.y * i1, k1 = -eC.y * i1;
     double a, c, z;
     {
       const double py = wave_prev(y), pg = wave_prev(g1), pk = wave_prev(k1);
@@ -759,16 +781,8 @@ __device__ __forceinline__ void cyclic_solve(RowF row, DF d, double (&x)[PMAX], 
       }
     } else {
       // one level of cyclic reduction: the couplings squared again, to the
-      // lanes two away.  An equation whose pivot all but vanished (a or c of 16
-      // and more; below 1 where the rows are diagonally dominant) would drown
-      // its neighbours in it, beyond what grow has seen: marked by a value that
-      // is not a number, such a system is left to interface_solve(), which
-      // eliminates in another order and measures that.  (Couplings of 3e5 cost
-      // 1e-8 of the solution where the other order errs by 1e-13.  On the high
-      // words, because two FP64 instructions more cost the adjoint 2%.)
-      const uint32_t ha = static_cast<uint32_t>(__double2hiint(a)) & 0x7fffffffu,
-                     hc = static_cast<uint32_t>(__double2hiint(c)) & 0x7fffffffu;
-      if (max(ha, hc) >= 0x40300000u) a = __hiloint2double(0x7ff80000, __double2loint(a));
+      // lanes two away
+      a = nan_if(drowns(1.0, a, c), a);
       const double am = wave_prev(a), cm = wave_prev(c), zm = wave_prev(z);
       const double ap = wave_next(a), cpn = wave_next(c), zp = wave_next(z);
       const double inv = rcp64(fma(-a, cm, fma(-c, ap, 1.0)));

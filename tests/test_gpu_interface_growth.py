@@ -34,10 +34,12 @@ def sch():
     S.sch_tune_set(S.TUNE_THREADS, 0)
 
 
+@np.errstate(divide="ignore", invalid="ignore")  # at a root of the pivot itself
 def eliminate(dv, NT, mu, dt):
     """The elimination on chunks of P rows: the largest |c'| of the
     chunks and of the odd interface equations, the even equations' pivots and
-    couplings, and the largest |a| + |c| after the reduction level."""
+    couplings, the largest |a| + |c| after the reduction level, and the odd
+    equations' pivots and couplings."""
     h = L / len(dv)
     o, d = h / 6 - mu * dt / (2 * h), 2 * h / 3 + mu * dt / h
     vm, vp = np.roll(dv, 1) / 4, np.roll(dv, -1) / 4
@@ -57,7 +59,28 @@ def eliminate(dv, NT, mu, dt):
     inv = 1 / (1 - a * np.roll(c, 1) - c * np.roll(a, -1))
     after = np.abs(a * np.roll(a, 1) * inv) + np.abs(c * np.roll(c, -1) * inv)
     quiet = max(np.abs(cp).max(), np.abs(ko).max())
-    return quiet, pivot, np.maximum(np.abs(a), np.abs(c)), after.max()
+    return quiet, pivot, np.maximum(np.abs(a), np.abs(c)), after.max(), (B[1::2], go, ko)
+
+
+def one_iteration(sch, dv, NT, mu, dt, seed):
+    """Status, and the errors of m and u against the oracle (of a refused step,
+    none: its input is kept)."""
+    nx = len(dv)
+    om = O.Model(L, 1.0, mu, dt, dv[None], picard_max=1)
+    m0, u0 = np.random.default_rng(seed + 1).standard_normal((1, nx)), np.zeros((1, nx))
+    _, m_ref, u_ref, _, _ = O.ensemble_window(om, m0, u0, np.ones((1, 1, 1)))
+    dev = dict(dtype=torch.float64, device="cuda")
+    gm = sch.Model(L, 1.0, mu, dt, torch.tensor(dv[None], **dev), picard_max=1)
+    m, u = torch.tensor(m0, **dev), torch.tensor(u0, **dev)
+    status = torch.full((1,), 99, dtype=torch.int32, device="cuda")
+    sch.sch_tune_set(sch.TUNE_THREADS, NT)
+    sch.sch_ensemble_step(gm, m, u, torch.ones((1, 1, 1), **dev), None, status)
+    sch.sch_tune_set(sch.TUNE_THREADS, 0)
+    err = [PR.rel_l2(a.cpu().numpy(), b) for a, b in ((m, m_ref), (u, u_ref))]
+    print(f"nx {nx}: status {int(status)}, error of m {err[0]:.2g}, of u {err[1]:.2g}", flush=True)
+    if int(status) == sch.SCH_E_UNSTABLE:
+        assert np.array_equal(m.cpu().numpy(), m0)
+    return int(status), *err
 
 
 # threads, a random field (its seed, mu, dt and scale), the even equation and the
@@ -94,7 +117,7 @@ def test_solve_with_a_small_even_pivot(sch, NT, seed, mu, dt, scale, eq, side, l
         lo, hi = (mid, hi) if (pivot(mid) > 0) == sign else (lo, mid)
     for e in range(4, 44):  # towards the root until the couplings are reached
         dv = field(lo * (1 + 2.0 ** -e))
-        quiet, _, couplings, after = eliminate(dv, NT, mu, dt)
+        quiet, _, couplings, after, _ = eliminate(dv, NT, mu, dt)
         if couplings.max() > reach:
             break
     print(f"nx {nx}: quiet {quiet:.3g}, even couplings {couplings.max():.3g}, after {after:.2g}",
@@ -102,19 +125,45 @@ def test_solve_with_a_small_even_pivot(sch, NT, seed, mu, dt, scale, eq, side, l
     # quiet everywhere else, and within the sweeps' bound after the level
     assert quiet < GROWTH_MAX / 4 and couplings.max() > reach and after < 2e-3
 
-    om = O.Model(L, 1.0, mu, dt, dv[None], picard_max=1)
-    m0, u0 = np.random.default_rng(seed + 1).standard_normal((1, nx)), np.zeros((1, nx))
-    _, m_ref, u_ref, _, _ = O.ensemble_window(om, m0, u0, np.ones((1, 1, 1)))
-    dev = dict(dtype=torch.float64, device="cuda")
-    gm = sch.Model(L, 1.0, mu, dt, torch.tensor(dv[None], **dev), picard_max=1)
-    m, u = torch.tensor(m0, **dev), torch.tensor(u0, **dev)
-    status = torch.full((1,), 99, dtype=torch.int32, device="cuda")
-    sch.sch_tune_set(sch.TUNE_THREADS, NT)
-    sch.sch_ensemble_step(gm, m, u, torch.ones((1, 1, 1), **dev), None, status)
-    sch.sch_tune_set(sch.TUNE_THREADS, 0)
-    err = PR.rel_l2(m.cpu().numpy(), m_ref)
-    print(f"status {int(status)}, error of m {err:.2g}", flush=True)
-    if int(status) == sch.SCH_E_UNSTABLE:
-        assert np.array_equal(m.cpu().numpy(), m0)  # the step's input is kept
-    else:
-        assert err < PR.REL_TOL and PR.rel_l2(u.cpu().numpy(), u_ref) < PR.REL_TOL
+    status, err_m, err_u = one_iteration(sch, dv, NT, mu, dt, seed)
+    assert status == sch.SCH_E_UNSTABLE or max(err_m, err_u) < PR.REL_TOL
+
+
+# the same for an odd equation (not the first of an eliminated run)
+ODD = [(256, 42, 0.01, 0.05, 0.30896666666666667, 55, 1, -0.07108192231364736,
+        -0.0609273619831263),
+       (256, 182, 1.0, 0.05, 10.292083333333334, 219, -1, -1.921542099556944,
+        -1.537233679645555),
+       (256, 379, 0.1, 0.025, 1.128166666666667, 231, 1, 1.254648844460772,
+        1.3442666190651127),
+       (512, 181, 0.01, 0.1, 0.02722760416666667, 275, -1, 0.023138679609350305,
+        0.02399566774302995),
+       (512, 652, 0.1, 0.1, 2.061020833333334, 173, 1, 1.3623273242984089,
+        1.5326182398357093)]
+
+
+@pytest.mark.parametrize("NT,seed,mu,dt,scale,eq,side,lo,hi", ODD)
+def test_solve_with_a_small_odd_pivot(sch, NT, seed, mu, dt, scale, eq, side, lo, hi):
+    """Systems that the order of interface_solve() solves to 1e-12 in m (it does
+    not meet this pivot): neither refused nor less accurate."""
+    nx = NT * P
+    base = scale * np.random.default_rng(seed).standard_normal(nx)
+    node = (eq * P + side) % nx
+
+    def field(s):
+        dv = base.copy()
+        dv[node] += s
+        return dv
+
+    def odd(s):
+        B, left, right = eliminate(field(s), NT, mu, dt)[4]
+        return B[eq // 2], max(abs(left[eq // 2]), abs(right[eq // 2]))
+
+    sign = odd(lo)[0] > 0
+    assert (odd(hi)[0] > 0) != sign
+    for _ in range(60):
+        mid = 0.5 * (lo + hi)
+        lo, hi = (mid, hi) if (odd(mid)[0] > 0) == sign else (lo, mid)
+    s = next(s for s in (lo * (1 + 2.0 ** -e) for e in range(4, 44)) if odd(s)[1] > 2.0 ** 19)
+    status, err_m, err_u = one_iteration(sch, field(s), NT, mu, dt, seed)
+    assert status != sch.SCH_E_UNSTABLE and err_m < 1e-12 and err_u < PR.REL_TOL
