@@ -449,8 +449,10 @@ __device__ __forceinline__ void spike_eliminate(const double (&A)[E], const doub
 // where chunks are long: a coupling falls by a factor per row (0.41 at the
 // 4096-node workloads, so 5e-7 over 16 rows).  Where every |A| + |C| is below
 // eps |B|, K sweeps s <- (R - A s_prev - C s_next) / B from s = R / B leave an
-// error below eps^(K+1) of the largest unknown; these bounds give 2^-57, a
-// sixteenth of the rounding of the result.
+// error below eps^(K+1) of the largest unknown within K + 1 equations; these
+// bounds give 2^-57, a sixteenth of the rounding of the result.  (2^-60, from
+// which on the reduction follows couplings, changed no error against 64 bits and
+// cost the windows and the adjoint 1%.)
 constexpr double kSweep2 = 0x1.0p-19, kSweep4 = 3.4e-4, kSweep6 = 3.4e-3;
 // Sweeps that the wavefront's equations s + a s_prev + c s_next = z take; 0 if
 // six are not enough.

@@ -6,6 +6,9 @@ couplings reach (a chunk of c nodes couples its ends by about r^c, r the root of
 the step matrix), so the same grids walk through the regimes.  Against the
 oracle's pivoted solve at the parity tolerance; a regime taken one step too
 early is off by its bound's square root and more."""
+import re
+from pathlib import Path
+
 import numpy as np
 import pytest
 
@@ -87,3 +90,66 @@ def test_cases_reach_every_regime():
     assert all(several["", k] for k in (2, 4, 6)) and several["level", 0], several
     assert any(several["level", k] for k in (2, 4, 6)), several
     assert all(any(one[n, k] for k in (2, 4)) for n in (0, 1, 2)), one
+
+
+def device_bounds():
+    """The device's bounds on the couplings, by the number of sweeps."""
+    src = (Path(__file__).parents[1] / "paper_2402_06927_amd" / "csrc" / "device.hpp").read_text()
+    line = re.search(r"constexpr double kSweep2 = .*?;", src, re.S).group()
+    got = {int(k): float.fromhex(v) if "x" in v else float(v)
+           for k, v in re.findall(r"kSweep(\d) = ([^,;]+)", line)}
+    assert sorted(got) == [2, 4, 6]
+    return got
+
+
+def test_sweeps_cut_off_below_rounding():
+    """K sweeps of couplings below eps leave eps^(K+1) of the largest unknown: at
+    most a sixteenth of a rounding."""
+    for k, eps in device_bounds().items():
+        assert eps ** (k + 1) <= 2.0 ** -57, (k, eps)
+
+
+# couplings that the reduction's last level still sees
+REDUCED = [(64, 64, 400.0), (100, 64, 400.0), (1000, 64, 400.0), (1024, 128, 400.0),
+           (1100, 256, 400.0), (2100, 512, 400.0)]
+
+
+@pytest.mark.parametrize("nx,threads,mu", REDUCED)
+def test_window_reduced_to_the_last_level(sch, nx, threads, mu):
+    test_window_across_coupling_regimes(sch, nx, threads, mu)
+
+
+def test_cases_reach_every_regime_of_the_device():
+    """As test_cases_reach_every_regime, by the device's own bounds, and with the
+    reduction that goes to its end: on one wavefront, and on several after the
+    elimination of interface_solve()."""
+    bounds = device_bounds()
+
+    def halve(e):  # couplings after every other unknown is eliminated
+        return e * e / 2 / (1 - e * e / 2)
+
+    def sweeps(e):
+        return next((k for k in (2, 4, 6) if e <= bounds[k]), 0)
+
+    one, several, to_the_end = set(), set(), set()
+    for nx, threads, mu in CASES + REDUCED:
+        e = coupling(W.BOOTSTRAP_256.scaled(nx=nx, mu=mu), threads)
+        if threads > 64:
+            e = halve(e)
+            after = sweeps(halve(e))
+            several.add(("window", sweeps(e)) if sweeps(e) else ("level", after))
+            if sweeps(e) or after:
+                continue
+            # the whole system: 64 equations, one for every threads / 64 chunks
+            e = coupling(W.BOOTSTRAP_256.scaled(nx=64 * (nx // 64), mu=mu), 64)
+        levels = 0
+        while e > bounds[4] and levels < 6:
+            e, levels = halve(e), levels + 1
+        if levels == 6:
+            to_the_end.add(threads)
+        if threads == 64:
+            one.add((min(levels, 2), 0 if levels == 6 else sweeps(e)))
+    assert {("window", k) for k in (2, 4, 6)} | {("level", 0)} <= several, several
+    assert any(("level", k) in several for k in (2, 4, 6)), several
+    assert all(any((n, k) in one for k in (2, 4)) for n in (0, 1, 2)), one
+    assert {64, 128, 256, 512} <= to_the_end, to_the_end
