@@ -110,8 +110,8 @@ def test_sweeps_cut_off_below_rounding():
 
 
 # couplings that the reduction's last level still sees
-REDUCED = [(64, 64, 400.0), (100, 64, 400.0), (1000, 64, 400.0), (1024, 128, 400.0),
-           (1100, 256, 400.0), (2100, 512, 400.0)]
+REDUCED = [(64, 64, 1000.0), (100, 64, 1000.0), (1000, 64, 1000.0), (1024, 128, 1000.0),
+           (1100, 256, 1000.0), (2100, 512, 1000.0)]
 
 
 @pytest.mark.parametrize("nx,threads,mu", REDUCED)
