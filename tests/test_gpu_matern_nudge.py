@@ -236,6 +236,19 @@ def test_jitter_matern_with_controls_parity(sch, nx, n, s, theta):
     np.testing.assert_array_equal(N(gl), dLam)  # the controls are read only
 
 
+@pytest.mark.parametrize("nx,threads,theta", [(65, 64, 0.1), (513, 64, 0.1), (1025, 128, 0.02),
+                                              (1025, 256, 0.1), (2049, 256, 0.1),
+                                              (4097, 512, 0.1)])
+def test_jitter_matern_with_controls_on_odd_grids(sch, nx, threads, theta):
+    """The same where the last cell of a row has no partner: its control, and its
+    share of the Girsanov term, on every number of threads."""
+    sch.sch_tune_set(sch.TUNE_THREADS, threads)
+    try:
+        test_jitter_matern_with_controls_parity(sch, nx, 4, 3, theta)
+    finally:
+        sch.sch_tune_set(sch.TUNE_THREADS, 0)
+
+
 def _gpu_nudged_cycle(sch, wl, m0, u0, y, sigma, n_jitter=3):
     gm = PR.gpu_model(wl)
     _, gmt = _mt(sch, wl)
