@@ -87,19 +87,22 @@ __device__ __forceinline__ double box_radius(double v) {
   p = fma(p, z, 1.0 / 7.0);
   p = fma(p, z, 1.0 / 5.0);
   p = fma(p, z, 1.0 / 3.0);
-  // ln 2 in two parts, the first with 20 trailing zero bits: its products with
-  // the exponent (at most 53) are exact
+  // ln 2 in two parts (Cody and Waite), the first with 20 trailing zero bits: its
+  // products with the exponent (at most 53) are exact.  2 s = f - s f takes f,
+  // which is exact, out of the series: what is rounded on the way is a sixth of
+  // the sum at most, and the sum's own rounding is kept (lo).
   constexpr double kLn2Hi = 0x1.62e42feep-1, kLn2Lo = 0x1.a39ef35793c76p-33;
   const double k = static_cast<double>(e);
-  const double l = fma(k, kLn2Hi, fma(2.0, s, fma(2.0 * s * z, p, k * kLn2Lo)));
-  // sqrt(x) by the coupled iteration for sqrt and its half reciprocal; x = 0
-  // (v = 1) has no reciprocal
+  const double a = fma(k, kLn2Hi, f), b = fma(s, fma(-2.0 * z, p, f), -k * kLn2Lo);
+  const double l = a - b, lo = (a - l) - b;
+  // sqrt(x) by the coupled iteration for sqrt and its half reciprocal, lo in its
+  // last residual; x = 0 (v = 1) has no reciprocal
   const double x = -2.0 * l, y = __builtin_amdgcn_rsq(x);
   double g = x * y, h = 0.5 * y;
   const double q = fma(-h, g, 0.5);
   g = fma(g, q, g);
   h = fma(h, q, h);
-  g = fma(fma(-g, g, x), h, g);
+  g = fma(fma(-2.0, lo, fma(-g, g, x)), h, g);
   return v < 1.0 ? g : 0.0;
 }
 

@@ -87,6 +87,23 @@ def test_radius(factors):
     assert np.abs((r[:-1] - ref[:-1]) / ref[:-1]).max() <= 3 * EPS
 
 
+def test_radius_no_worse_than_the_library(factors):
+    """The device library's sqrt(-2 log v) errs by 1.66e-16 at most, the factor by
+    no more than its root's rounding, half a rounding of the sum's first part
+    (which lies in its log, at most 1.25 times as large) and half of three
+    roundings of the quarter that the series makes: 2 EPS, 2.2e-16.  Where the
+    exponent is 0 (v in [0.707, 1)) that first part is exact, and the series a
+    sixth: 1.25 EPS, 1.4e-16."""
+    v = _radius_points()[:-1]
+    k = np.random.default_rng(3).integers(int(2 ** 53 * 0.3), 2 ** 53, 400000)
+    v = np.concatenate([v, k.astype(np.float64) * EPS])
+    r, _, _ = factors(v, np.zeros_like(v))
+    ref = np.sqrt(-2 * np.log(v.astype(np.longdouble)))
+    err = np.abs((r - ref) / ref)
+    assert err.max() <= 2 * EPS
+    assert err[v >= 0.7072].max() <= 1.25 * EPS
+
+
 def test_sine_and_cosine(factors):
     u = _angle_points()
     _, s, c = factors(np.full_like(u, 0.5), u)
