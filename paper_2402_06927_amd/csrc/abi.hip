@@ -98,7 +98,9 @@ struct GatherField {
 };
 int resample_rows(int n, std::initializer_list<GatherField> fields, const int* idx,
                   double* scratch, hipStream_t st) {
-  if (n <= kGatherRows) {
+  int64_t bytes = 0;
+  for (const GatherField& f : fields) bytes += static_cast<int64_t>(sizeof(double)) * n * f.len;
+  if (n <= kGatherFewRows || (n <= kGatherRows && bytes <= kGatherBytes)) {
     GatherSet G{};
     G.n = n;
     for (const GatherField& f : fields) {

@@ -155,3 +155,26 @@ def test_rows_resampled_in_a_cycle(sch, nx, n):
     assert st["resampled"] == 1 and abs(st["ess"] - st_o.ess) < 1e-9 * st_o.ess
     assert PR.rel_l2(m.cpu().numpy(), m_o) < PR.REL_TOL
     assert PR.rel_l2(u.cpu().numpy(), u_o) < PR.REL_TOL
+
+
+@pytest.mark.parametrize("n,n_steps", [(128, 256), (129, 256)])
+def test_long_rows_resampled_in_a_cycle(sch, n, n_steps):
+    """A tempered cycle whose increments' rows are long (one value per cell and
+    step, over 256 MiB in all), on both sides of the rows up to which these change
+    places in LDS.  Each step of either side errs by the
+    tolerance 1e-13 at most: 5e-11 in all."""
+    wl = W.MATERN_4096.scaled(nx=1024, n_steps=n_steps, n_obs=40, n_particles=n, eta=0.1, dt=0.01)
+    om, gm = PR.oracle_model(wl), PR.gpu_model(wl)
+    omt = O.matern(wl.kappa, wl.eta, wl.k_solves)
+    gmt = sch.Matern(wl.kappa, wl.eta, wl.k_solves)
+    u0, m0, _, _ = PR.prior(wl, n)
+    y, sig = O.observe(u0[0], wl.n_obs), np.full(wl.n_obs, 1.0)
+    args = (n_steps, 0.9 * n, 50, 0.9, 1, 3)
+    rc, out, st_o = O.tempered_cycle_matern(om, omt, y, sig, wl.seed, 0, m0, u0, *args)
+    m, u = _dev(m0), _dev(u0)
+    st = sch.sch_pf_tempered_cycle_matern(gm, gmt, sch.Obs(_dev(y), _dev(sig)), wl.seed, 0, m, u,
+                                          *args,
+                                          sch.matern_workspace(sch.WS_TEMPERED, gm, n, n_steps, 1))
+    assert rc == 0 and st["n_temper"] == st_o.n_temper and st["n_accept"] == st_o.n_accept
+    assert PR.rel_l2(m.cpu().numpy(), out["m"]) < PR.REL_TOL
+    assert PR.rel_l2(u.cpu().numpy(), out["u"]) < PR.REL_TOL
