@@ -115,9 +115,9 @@ __device__ __forceinline__ void advect_t(const double (&s)[PMAX], double sl, dou
 // One reverse step: lam holds lambda_{n+1} on entry and lambda_n on exit,
 // gdU receives dJ/d(dU^n).  s = m^n + m^{n+1} and w = dv/4 + o of the step
 // (o = h/6 - mu dt/(2h)) come from the forward sweep; rows of A^T:
-// (w_i, 2h/3 + mu dt/h + w_{i+1} - w_{i-1}, 2 o - w_i).  Where the window's two
-// LDS arrays exist (free during the reverse sweep), s and lambda_{n+1}, which
-// the fixed-point loop only reads, wait there instead of in registers.  As in
+// (w_i, 2h/3 + mu dt/h + w_{i+1} - w_{i-1}, 2 o - w_i).  s and
+// lambda_{n+1}, which the fixed-point loop only reads, wait in the window's two
+// LDS arrays, free during the reverse sweep, instead of in registers.  As in
 // the forward step an iteration has two barriers: the halo of nu comes from
 // the interface values, and the stopping test rides on the Helmholtz solve
 // (whose result the last iteration does not use: one solve a step, where the
@@ -127,7 +127,6 @@ __device__ int adjoint_step(const StepParams& P, const HelmConst& K, const doubl
                             const double (&w)[PMAX], double (&lam)[PMAX], double (&gdU)[PMAX],
                             const Chunk& ch, RowLds<NT>& L, AuxLds<PMAX, NT>& X, int t,
                             Parity& par, int& iters) {
-  constexpr bool kL = AuxLds<PMAX, NT>::kInLds;
   const int cnt = ch.cnt;
   double sl, sr, wl, wr;
   {
@@ -148,26 +147,21 @@ __device__ int adjoint_step(const StepParams& P, const HelmConst& K, const doubl
     b = ad + (vp - vm);
     c = ao2 - w[j];
   };
-  // s and lambda_{n+1} from LDS (kL), each value laundered so that the
+  // s and lambda_{n+1} from LDS, the column laundered so that the
   // loads stay inside the loop instead of being hoisted into registers
   int tx = t;
   auto s_at = [&](double (&sv)[PMAX]) {
 #pragma unroll
-    for (int j = 0; j < PMAX; ++j) sv[j] = kL ? X.at(kL ? 1 : 0, j, tx) : s[j];
+    for (int j = 0; j < PMAX; ++j) sv[j] = X.at(1, j, tx);
   };
-  auto lam_at = [&](int j) -> double {
-    if constexpr (kL) return X.at(0, j, tx);
-    else return lam[j];
-  };
+  auto lam_at = [&](int j) -> double { return X.at(0, j, tx); };
   double nu[PMAX], rhs[PMAX];
 #pragma unroll
   for (int j = 0; j < PMAX; ++j) {
     nu[j] = 0.0;
     rhs[j] = lam[j];
-    if constexpr (kL) {
-      X.at(0, j, t) = lam[j];
-      X.at(1, j, t) = s[j];
-    }
+    X.at(0, j, t) = lam[j];
+    X.at(1, j, t) = s[j];
   }
   // the first solve gives A^{-T} lambda; picard_max corrections follow at most
   int status = SCH_E_NONCONVERGED, k = 1;

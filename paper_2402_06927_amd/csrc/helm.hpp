@@ -21,7 +21,6 @@ namespace sch {
 
 struct HelmConst {
   double r, coef;   // root and 1/(kappa (1 - r^2)), kappa = -o / r
-  double rinv;      // 1 / r
   double rN1;       // 1/(1 - r^nx)
   double rb, rb1;   // r^base, r^(base+1): multipliers of chunks of base / base+1 rows
   int base;         // nx / NT

@@ -123,7 +123,6 @@ inline HelmConst make_helm_op(double h, int nx, double a2, const Tile& tl) {
   K.base = nx / tl.nt;
   K.rb = std::pow(K.r, static_cast<double>(K.base));
   K.rb1 = std::pow(K.r, static_cast<double>(K.base + 1));
-  K.rinv = 1.0 / K.r;
   K.iho = 1.0 / K.ho;
   K.mh6 = h / 6.0;
   K.mh23 = 2.0 * h / 3.0;

@@ -55,17 +55,12 @@ struct Parity {
 
 // Two per-node arrays of the window (the explicit part of dv and the previous
 // Picard iterate) live in LDS, a thread's slots in pairs (an LDS read of 16
-// bytes a lane moves twice what two of 8 do in its time), when they fit next to the
-// solver's LDS (128 KiB for both: a workgroup may hold up to 160 KiB); when
-// only one fits, the explicit part goes to LDS and the iterate stays in
-// registers; otherwise both do.
+// bytes a lane moves twice what two of 8 do in its time): at most 128 KiB for
+// both, next to the solver's own (a workgroup may hold up to 160 KiB).
 template <int PMAX, int NT>
 struct AuxLds {
-  static constexpr size_t kBytes = static_cast<size_t>(PMAX) * NT * sizeof(double);
-  static constexpr bool kInLds = 2 * kBytes <= 131072;  // both arrays
-  static constexpr bool kDInLds = kBytes <= 65536;     // the explicit part
-  static_assert(kDInLds && PMAX % 2 == 0, "the explicit part is in LDS on every tile");
-  alignas(16) double a[kInLds ? 2 : 1][PMAX / 2][NT][2];
+  static_assert(PMAX % 2 == 0 && 2 * PMAX * NT * sizeof(double) <= 131072, "both fit");
+  alignas(16) double a[2][PMAX / 2][NT][2];
   __device__ double& at(int s, int j, int t) { return a[s][j / 2][t][j % 2]; }
   __device__ const double& at(int s, int j, int t) const { return a[s][j / 2][t][j % 2]; }
   // the explicit part's PMAX NT words, free from a step's last solve to the
@@ -386,7 +381,6 @@ __device__ int run_window(const StepParams& P, const HelmConst& K, NoiseF noise,
                           double (&m)[PMAX], double (&u)[PMAX], const Chunk& ch, RowLds<NT>& L,
                           AuxLds<PMAX, NT>& X, int t, Parity& par, int& iters,
                           SinkF sink = {}) {
-  constexpr bool kLds = AuxLds<PMAX, NT>::kInLds;
   const int cnt = ch.cnt;
   const double hdt = 0.5 * P.dt;
   // dv is carried as dv/4, the form in which it enters the rows of A (exact:
@@ -394,15 +388,14 @@ __device__ int run_window(const StepParams& P, const HelmConst& K, NoiseF noise,
   const double hdt4 = 0.25 * hdt;
   const double f1 = P.h / 3.0, f0 = 4.0 * P.h / 3.0;  // 2 M: (h/3, 4h/3, h/3)
   const bool bordered = FULL || K.base >= 2;
-  double rP[kLds ? 1 : PMAX];
   // The thread's column of the LDS arrays.  It is laundered once per Picard
   // iteration, so the loads of the step's invariants are redone inside the
   // iteration (not hoisted into registers) and still issue back to back.
   int tx = t;
   auto getD = [&](int j) -> double { return X.at(0, j, tx); };
   auto setD = [&](int j, double v) { X.at(0, j, tx) = v; };
-  auto getP = [&](int j) -> double { if constexpr (kLds) return X.at(1, j, tx); else return rP[j]; };
-  auto setP = [&](int j, double v) { if constexpr (kLds) X.at(1, j, tx) = v; else rP[j] = v; };
+  auto getP = [&](int j) -> double { return X.at(1, j, tx); };
+  auto setP = [&](int j, double v) { X.at(1, j, tx) = v; };
   for (int n = 0; n < n_steps; ++n) {
     // (dU^n + dt/2 u^n) / 4 + o, the explicit part of dv / 4 + o
     double eL, eR, mL, mR, uL, uR;
@@ -561,15 +554,12 @@ __device__ int run_window(const StepParams& P, const HelmConst& K, NoiseF noise,
 // Point o lies in cell e = floor(o nx / n_obs) at fraction
 // r = (o nx - e n_obs) / n_obs; the thread finds its first point with one
 // integer division and walks on with integer multiplications only.
-// `extra` is a per-thread addend summed into the result (0 for the plain
-// likelihood).
 template <int PMAX, int NT, bool FULL>
 __device__ double block_nll(const double (&u)[PMAX], const Chunk& ch, int nx, int n_obs,
-                            const double* y, const double* sigma, RowLds<NT>& L, int t, int& hs,
-                            double extra = 0.0) {
+                            const double* y, const double* sigma, RowLds<NT>& L, int t, int& hs) {
   double hl, hr;
   halo<PMAX, NT, FULL>(u, ch.cnt, L, t, hl, hr, hs);
-  double acc = 2.0 * extra;
+  double acc = 0.0;
   int64_t o = (static_cast<int64_t>(ch.start) * n_obs + nx - 1) / nx;
   const double dn = static_cast<double>(n_obs);
 #pragma unroll
@@ -600,10 +590,11 @@ __device__ __forceinline__ double staged_at(const AuxLds<PMAX, NT>& X, int slot,
 }
 
 // The likelihood of block_nll with the velocity staged in auxiliary LDS
-// slot 0: one thread per observation point.
+// slot 0: one thread per observation point.  `extra` is a per-thread addend
+// summed into the result (the Girsanov term).
 template <int PMAX, int NT>
 __device__ double staged_nll(const AuxLds<PMAX, NT>& X, int nx, int n_obs, const double* y,
-                             const double* sigma, RowLds<NT>& L, int t, double extra = 0.0) {
+                             const double* sigma, RowLds<NT>& L, int t, double extra) {
   const double dn = static_cast<double>(n_obs);
   double acc = 2.0 * extra;
   for (int o = t; o < n_obs; o += NT) {
@@ -913,20 +904,15 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) k_
       }
     }
     bool accept = false;
-    double phin;
-    if constexpr (AuxLds<PMAX, NT>::kInLds) {
-      // stage the end state (u in slot 0, m in slot 1): no chunk arrays stay
-      // live through the likelihood and the copy-out
+    // stage the end state (u in slot 0, m in slot 1): no chunk arrays stay
+    // live through the likelihood and the copy-out
 #pragma unroll
-      for (int jj = 0; jj < PMAX; ++jj) {
-        X.at(0, jj, t) = u[jj];
-        X.at(1, jj, t) = m[jj];
-      }
-      __syncthreads();
-      phin = staged_nll<PMAX, NT>(X, nx, A.n_obs, A.y, A.sigma, L, t, girs);
-    } else {
-      phin = block_nll<PMAX, NT, FULL>(u, ch, nx, A.n_obs, A.y, A.sigma, L, t, par.hs, girs);
+    for (int jj = 0; jj < PMAX; ++jj) {
+      X.at(0, jj, t) = u[jj];
+      X.at(1, jj, t) = m[jj];
     }
+    __syncthreads();
+    double phin = staged_nll<PMAX, NT>(X, nx, A.n_obs, A.y, A.sigma, L, t, girs);
     if (st != SCH_OK || !isfinite(phin)) phin = INFINITY;
     double v;
     if constexpr (MATERN)
@@ -945,16 +931,11 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) k_
       } else {
         for (int i = t; i < S * Q; i += NT) cur[i] = prop[i];
       }
-      if constexpr (AuxLds<PMAX, NT>::kInLds) {
-        double* me = A.m_end + static_cast<size_t>(p) * nx;
-        double* ue = A.u_end + static_cast<size_t>(p) * nx;
-        for (int i = t; i < nx; i += NT) {
-          me[i] = staged_at(X, 1, nx, i);
-          ue[i] = staged_at(X, 0, nx, i);
-        }
-      } else {
-        store_chunk<PMAX, FULL>(A.m_end + static_cast<size_t>(p) * nx, ch, m);
-        store_chunk<PMAX, FULL>(A.u_end + static_cast<size_t>(p) * nx, ch, u);
+      double* me = A.m_end + static_cast<size_t>(p) * nx;
+      double* ue = A.u_end + static_cast<size_t>(p) * nx;
+      for (int i = t; i < nx; i += NT) {
+        me[i] = staged_at(X, 1, nx, i);
+        ue[i] = staged_at(X, 0, nx, i);
       }
       phi = phin;
       ++acc;
