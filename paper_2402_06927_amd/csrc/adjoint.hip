@@ -4,5 +4,8 @@
 
 namespace sch {
 #define SCH_DEFINE(PM, NT, FULL) SCH_ADJOINT_KERNELS(, PM, NT, FULL)
+SCH_TILES_OWN_ADJOINT(SCH_DEFINE)
+#undef SCH_DEFINE
+#define SCH_DEFINE(PM, NT, FULL) SCH_ADJOINT_MATERN_KERNELS(, PM, NT, FULL)
 SCH_TILES(SCH_DEFINE)
 }  // namespace sch

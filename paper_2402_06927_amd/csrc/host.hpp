@@ -74,6 +74,16 @@ inline Tile tile_for(int nx, int nt) {
   return tl;
 }
 
+// Whether the modes-form adjoint runs on twice the tile's threads.  It holds more
+// per node than the window (the reverse sweep's source, checkpoints, the
+// transposed solve's right-hand side): on 16 nodes per thread it spilled and ran
+// 7-110% slower than on twice the threads with 8 nodes each at every grid
+// measured.  12 slots follow the same rule, which is the better one for few
+// particles (20 steps, doubled / as they are: 1500 nodes 778 / 1016 us at 128
+// particles; 3000 nodes 1107 / 1220 us), not for many (700 nodes 961 / 771 us at
+// 512; 1500 nodes 3811 / 2950 us, 3000 nodes 8696 / 6103 us at 2048).
+constexpr bool doubles_adjoint(int nt, int pmax) { return pmax > 8 && nt <= 256; }
+
 // The kernels take every chunk to hold at least kMinRows<PMAX> rows (their
 // ragged-chunk masks start there).
 inline bool tile_rows_ok(int nx, const Tile& tl) {

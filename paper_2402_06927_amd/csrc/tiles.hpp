@@ -18,8 +18,9 @@ namespace sch {
 #define SCH_JITTER_MATERN_KERNELS(LINK, PM, NT, FULL)                                        \
   LINK template __global__ void k_jitter<PM, NT, FULL, true, false>(JitterArgs, HelmConst);  \
   LINK template __global__ void k_jitter<PM, NT, FULL, true, true>(JitterArgs, HelmConst);
-#define SCH_ADJOINT_KERNELS(LINK, PM, NT, FULL)                                            \
-  LINK template __global__ void k_nudge_grad<PM, NT, FULL, false>(NudgeArgs, HelmConst);   \
+#define SCH_ADJOINT_KERNELS(LINK, PM, NT, FULL) \
+  LINK template __global__ void k_nudge_grad<PM, NT, FULL, false>(NudgeArgs, HelmConst);
+#define SCH_ADJOINT_MATERN_KERNELS(LINK, PM, NT, FULL) \
   LINK template __global__ void k_nudge_grad<PM, NT, FULL, true>(NudgeArgs, HelmConst);
 #define SCH_BATCH_KERNELS(LINK, PM, NT) \
   LINK template __global__ void k_batch_window<PM, NT>(BatchDev, const int*, int, unsigned int*);
@@ -29,8 +30,11 @@ namespace sch {
   SCH_WINDOW_KERNELS(extern, PM, NT, FULL)    \
   SCH_JITTER_KERNELS(extern, PM, NT, FULL)    \
   SCH_JITTER_MATERN_KERNELS(extern, PM, NT, FULL) \
-  SCH_ADJOINT_KERNELS(extern, PM, NT, FULL)
+  SCH_ADJOINT_MATERN_KERNELS(extern, PM, NT, FULL)
 SCH_TILES(SCH_DECLARE)
+#undef SCH_DECLARE
+#define SCH_DECLARE(PM, NT, FULL) SCH_ADJOINT_KERNELS(extern, PM, NT, FULL)
+SCH_TILES_OWN_ADJOINT(SCH_DECLARE)
 #undef SCH_DECLARE
 #define SCH_DECLARE(PM, NT) SCH_BATCH_KERNELS(extern, PM, NT)
 SCH_BATCH_TILES(SCH_DECLARE)
