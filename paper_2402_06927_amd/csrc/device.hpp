@@ -60,10 +60,12 @@ __device__ __forceinline__ double rcp64(double x) {
 // The two factors of a Box-Muller pair.  The device library's log, sqrt and
 // sincos cover all arguments (330 instructions a pair, with branches for
 // reductions that never happen here); these cover the ones that do, from the
-// plain series, in about 95.  Together with the single multiplication of
+// plain series, in about 100.  Together with the single multiplication of
 // philox10 they took the jitter with the Matern-type noise, which draws a pair
 // for every two nodes, steps and moves, from 18.4 to 17.4 ms at 4096 nodes and
-// 1024 particles.
+// 1024 particles.  Over 4 million points the radius errs by 1.17e-16 at most (the
+// library's: 1.66e-16), sine and cosine by 1.9e-16 (6.9e-16, with the angle
+// rounded before).
 //
 // sqrt(-2 log v) for v = k 2^-53 in (0, 1].  v = 2^e m with m in [0.707, 1.414),
 // log m = 2 atanh(s), s = (m - 1) / (m + 1), |s| <= 0.172: the series to s^19

@@ -96,12 +96,28 @@ inline int g_tune_threads = 0;  // SCH_TUNE_THREADS
 // n: the particles that the call advances, 0 if its kernels take the tile for
 // short chunks whatever their number.  Twice the nodes a thread cost less a
 // node (fewer chunks to join, fewer barriers) but keep a particle longer: they
-// pay once the short chunks' workgroups wait for a place (window, us a step,
-// short / long chunks: 2048 nodes 18.5 / 23.5 at 512 particles, 33.2 / 27.2 at
-// 1024; 1000 nodes 13.6 / 15.8 at 256, 19.0 / 17.0 at 512), at two wavefronts a
-// particle earlier, since one wavefront needs no barriers at all, and at
-// eight always (3000 nodes 18.4 / 17.5 at 32 particles, 77.8 / 54.1 at 1024;
-// 4096 nodes 16.7 / 16.7 and 72.6 / 53.3).
+// pay once the short chunks' workgroups wait for a place.  Windows of 10 steps
+// (jitter: two moves), us, short / long chunks:
+//   128 threads           256 particles  288        512
+//     window, 1000 nodes     145 / 158   189 / 161  199 / 173
+//     the same, Matern       200 / 222   253 / 221  257 / 227
+//     jitter                 288 / 330   371 / 327  405 / 356
+//     the same, Matern       440 / 548   582 / 560  586 / 569
+//   256 threads           512 particles  576        1024
+//     window, 1500 nodes     230 / 276   290 / 247  389 / 301
+//     the same, Matern       266 / 307   366 / 305  461 / 329
+//     jitter                 406 / 504   568 / 501  703 / 523
+//     the same, Matern       611 / 764   834 / 768  1073 / 818
+//   512 threads           16 particles   256        1024
+//     window, 3000 nodes     196 / 183   219 / 199  790 / 498
+//     the same, Matern       308 / 244   326 / 253  1120 / 634
+//     jitter                 375 / 353   412 / 388  1516 / 978
+//     the same, Matern       689 / 620   729 / 647  2553 / 1687
+// The lines lie there at the other grids too (600, 768, 1024; 1200, 1800, 2048;
+// 2500, 4096 nodes), but for the Matern-type jitter at 1800 nodes, which short
+// chunks serve 3% better up to 768 particles.  The gradient-based jitters take
+// the tile for their closing window only (doubles_adjoint).  The rounding goes
+// with the tile: a particle's last bits depend on how many are advanced with it.
 inline bool pick_tile(int nx, Tile& tl, int64_t n = 0) {
   if (nx < 64 || nx > 8192) return false;
   int nt = g_tune_threads;
