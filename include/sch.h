@@ -821,13 +821,14 @@ int sch_mlp_controls(int32_t n, int32_t cols, const float *Y, const float *mean,
  * particle of the model kernels (a power of two in 64..512; 0 = automatic:
  * the smallest power of two giving at most 8 nodes per thread; half of it for
  * more than 256 particles a call at 128 threads, for more than 512 at 256, and
- * always from 2049 to 4096 nodes; sch_nudge_*,
- * sch_pf_nudged_cycle_matern and the calls that only solve take the former).  The summation orders go with the threads: under the automatic
- * choice a particle's result can differ in its last bits between ensembles on
- * either side of these lines (an ensemble advanced whole or in parts); a value
- * set here makes it independent of the ensemble.  A value that leaves more than
- * 16 nodes per thread, or fewer than one, makes the model calls return
- * SCH_E_SHAPE.  sch_tune_get returns the current value (-1 for an unknown key).
+ * always from 2049 to 4096 nodes; sch_nudge_*, sch_pf_nudged_cycle_matern and
+ * the calls that only solve take the former).  The summation orders go with the
+ * threads: under the automatic choice a particle's result can differ in its last
+ * bits between ensembles on either side of these lines (an ensemble advanced
+ * whole or in parts); a value set here makes it independent of the ensemble.
+ * The batched runner counts the particles launched together.  A value that
+ * leaves more than 16 nodes per thread, or fewer than one, makes the model calls
+ * return SCH_E_SHAPE.  sch_tune_get returns the current value (-1 for an unknown key).
  * ------------------------------------------------------------------------ */
 #define SCH_TUNE_THREADS 2
 int sch_tune_set(int32_t key, int32_t value);
