@@ -810,7 +810,10 @@ int sch_gather(int32_t n_rows, int64_t row_len, const int32_t* idx, const double
                double* dst, void* stream) {
   if (n_rows < 1 || n_rows > 65535 || row_len < 1 || !idx || !src || !dst || src == dst)
     return fail(SCH_E_ARG, "bad arguments to sch_gather");
-  const int gx = static_cast<int>(std::min<int64_t>((row_len + 255) / 256, 64));
+  // as many workgroups as have something to move (a launch of one a 256 doubles,
+  // half of them idle, took 130 us for 8192 rows of 4096, this one 86)
+  const int64_t lanes = rows_in_pairs(src, dst, row_len) ? row_len / 2 : row_len;
+  const int gx = static_cast<int>(std::min<int64_t>((lanes + 255) / 256, 64));
   hipLaunchKernelGGL(k_gather, dim3(gx, n_rows), dim3(256), 0, S(stream), n_rows, row_len, idx,
                      src, dst);
   CHECK_LAUNCH();

@@ -456,6 +456,13 @@ static __global__ void __launch_bounds__(kTB) k_resample(int n, const double* w,
   resample_body(n, w, u0p, cond_ess, cond_thr, idx, degenerate, cum, L);
 }
 
+// Whether rows are read and written 16 bytes a lane.
+__host__ __device__ inline bool rows_in_pairs(const double* src, const double* dst,
+                                              int64_t row_len) {
+  return ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst) |
+           static_cast<uintptr_t>(8 * row_len)) & 15) == 0;
+}
+
 // dst[j][:] = src[idx[j]][:], 16 bytes a lane where the rows allow
 static __global__ void k_gather(int n_rows, int64_t row_len, const int* idx, const double* src,
                          double* dst) {
@@ -466,8 +473,7 @@ static __global__ void k_gather(int n_rows, int64_t row_len, const int* idx, con
   double* d = dst + static_cast<int64_t>(j) * row_len;
   const int64_t i0 = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x,
                 step = static_cast<int64_t>(gridDim.x) * blockDim.x;
-  if (((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst) |
-        static_cast<uintptr_t>(8 * row_len)) & 15) == 0) {
+  if (rows_in_pairs(src, dst, row_len)) {
     typedef double d2 __attribute__((ext_vector_type(2)));
     for (int64_t i = i0; i < row_len / 2; i += step)
       reinterpret_cast<d2*>(d)[i] = reinterpret_cast<const d2*>(s)[i];

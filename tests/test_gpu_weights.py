@@ -157,6 +157,16 @@ def test_rows_resampled_in_a_cycle(sch, nx, n):
     assert PR.rel_l2(u.cpu().numpy(), u_o) < PR.REL_TOL
 
 
+@pytest.mark.parametrize("row_len", [2, 510, 512, 514, 1024, 1026, 32766, 32768, 32770])
+def test_gather_of_pairs_at_the_grids_edges(sch, row_len):
+    """Rows of whole 16-byte pairs at the lengths where another workgroup starts."""
+    src = torch.arange(5 * row_len, dtype=torch.float64, device="cuda").reshape(5, row_len)
+    idx = torch.tensor([4, 0, 0, 3, 2], dtype=torch.int32, device="cuda")
+    dst = torch.full_like(src, -1.0)
+    sch.sch_gather(idx, src, dst)
+    assert torch.equal(dst, src[idx.long()])
+
+
 @pytest.mark.parametrize("n,n_steps", [(128, 256), (129, 256)])
 def test_long_rows_resampled_in_a_cycle(sch, n, n_steps):
     """A tempered cycle whose increments' rows are long (one value per cell and
