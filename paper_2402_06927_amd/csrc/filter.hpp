@@ -488,13 +488,13 @@ static __global__ void k_gather(int n_rows, int64_t row_len, const int* idx, con
 // them.  Rows that stay are left alone, as are those of an index out of range.
 //
 // Up to kGatherRows rows fit 64 KB, two workgroups a compute unit (six fields,
-// one launch / gathers and copies: 256 nodes, 512 rows 16 / 31 us; 4096 nodes
-// 61 / 72 us; with 768 rows, one workgroup a unit, 138 / 86 us).  Each row is a
+// one launch / gathers and copies: 256 nodes, 512 rows 16 / 37 us; 4096 nodes
+// 61 / 68 us; with 768 rows, one workgroup a unit, 138 / 80 us).  Each row is a
 // stream of its own, so that beside many rows the fields have to stay in the
 // last-level cache: at 200 to 512 rows the lines cross between 280 and 400 MB
-// (512 rows, 240 MB 170 / 210 us, 280 MB 257 / 229 us, 369 MB 361 / 279 us; 256
-// rows, 250 MB 120 / 200 us, 350 MB 248 / 258 us, 450 MB 357 / 340 us); at 64 and
-// 128 rows not at all (128 rows, 250 MB 93 / 204 us, 1.2 GB 688 / 919 us).
+// (512 rows, 240 MB 173 / 200 us, 280 MB 232 / 221 us, 369 MB 355 / 272 us; 256
+// rows, 250 MB 119 / 195 us, 350 MB 249 / 259 us, 450 MB 366 / 339 us); at 64 and
+// 128 rows not at all (128 rows, 250 MB 98 / 203 us, 1.2 GB 683 / 971 us).
 constexpr int kGatherRows = 512, kGatherCols = 16;
 constexpr int kGatherFewRows = 128;
 constexpr int64_t kGatherBytes = int64_t(256) << 20;
